@@ -575,7 +575,7 @@ static void launch_cop(int cf, int msg, dim3 g, dim3 bl, size_t lds, hipStream_t
     else if (cf == 1) launch_cop_v<kGrad, 1>(msg, g, bl, lds, st, A);
     else if (cf == 2) launch_cop_v<kGrad, 2>(msg, g, bl, lds, st, A);
     else if (cf == 3) launch_cop_v<kGrad, 3>(msg, g, bl, lds, st, A);
-    else launch_cop_v<kGrad, 1>(msg, g, bl, lds, st, A);   // 4: level 1 beside the tiles
+    else launch_cop_v<kGrad, 4>(msg, g, bl, lds, st, A);
 }
 
 fsmt_status allow_lds(const void *fn, size_t bytes) {
@@ -891,8 +891,9 @@ static fsmt_status cop_launch(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, doub
         }
     } else if (h->n_big < h->n_cons) {
         if (A.n_tasks > 0) {
-            if (grad) launch_cop<true>(cf, msg, g, bl, lds, st, A);
-            else launch_cop<false>(cf, msg, g, bl, lds, st, A);
+            const int lcf = untiled_level(cf, h->n_window > 0);
+            if (grad) launch_cop<true>(lcf, msg, g, bl, lds, st, A);
+            else launch_cop<false>(lcf, msg, g, bl, lds, st, A);
             if ((rc = launch_status("cop kernel"))) return rc;
         }
         if (h->n_tiles > 0) {

@@ -1078,8 +1078,12 @@ __device__ __forceinline__ float task_eval(const TabView &T, const TaskCtx &t, c
         if constexpr (kCF >= 3) {
             if (t.B.pad == -2)
                 return window_eval<kGrad>(T, t, T.gd[t.B.tpl].neg, st, kappa, hard, wc, sc, lane);
+        } else {
+            // no launch sends a window here (untiled_level); its template has neither a guarded
+            // disjunction's record nor room in the message store, so it must not fall through
+            if (t.B.pad == -2) return __builtin_nanf("");
         }
-        if (t.B.pad < 0) {
+        if (t.B.pad == -1) {
             const GdInfo g = load_gd(T.gd + t.B.tpl);
             const int NB = t.B.n_bslots, NA = t.B.n_slots - t.B.n_bslots;
             if (NB <= 1 && NA <= 2) return gd_eval_n<1, 2, kGrad, kSlim>(T, t, g, st, kappa, hard, wc, sc, lane);
@@ -1109,6 +1113,9 @@ inline int closed_level(const fsmt_xbdd *h) {
     if ((h->tile_kinds & kTileBits) || h->n_window > 0) return h->gd_level <= 1 ? 4 : 3;
     return h->tile_kinds ? (h->gd_level > 1 ? h->gd_level : 1) : h->gd_level;
 }
+// The level of a launch that sweeps the untiled templates alone (their tiles run in a kernel of
+// their own): level 4 without a window leaves level 1's families.
+inline int untiled_level(int cf, bool windows) { return cf == 4 && !windows ? 1 : cf; }
 // The level that serves two instances of one launch.
 inline int closed_level_of(int a, int b) {
     if (a == b) return a;

@@ -649,7 +649,8 @@ fsmt_status solve_impl(const fsmt_xbdd *const *insts, int32_t n_inst, const fsmt
                 plan.wg_lds = wg_lds;
                 plan.cf = 0;
                 for (size_t q = 0; q < ib.size(); ++q)
-                    if (!gi[q].slices) plan.cf = closed_level_of(plan.cf, closed_level(insts[ib[q]]));
+                    if (!gi[q].slices)
+                        plan.cf = closed_level_of(plan.cf, untiled_level(closed_level(insts[ib[q]]), insts[ib[q]]->n_window > 0));
                 // each replay of the level sequence advances every running restart by one
                 // level (the kernels read each restart's level from memory and skip finished
                 // restarts); levels below level_begin are complete by the caller's word, so

@@ -445,8 +445,8 @@ static fsmt_status enqueue_level(const GridInst *d_insts, int n_inst, const Grid
             launch_sweep<2>(P, g, b, st, d_insts, n_inst, S);
         else if (P.cf == 3)
             launch_sweep<3>(P, g, b, st, d_insts, n_inst, S);
-        else   // 4: level 1 beside the tiles
-            launch_sweep<1>(P, g, b, st, d_insts, n_inst, S);
+        else
+            launch_sweep<4>(P, g, b, st, d_insts, n_inst, S);
         if ((rc = launch_status("grid sweep"))) return rc;
         if (S.tile_tasks > 0) {
             hipLaunchKernelGGL(grid_tile_kernel, dim3((unsigned)((S.tile_tasks + 3) / 4)), dim3(256), 0, st, d_insts,
