@@ -170,13 +170,15 @@ static bool prefer_grid(const fsmt_xbdd *h, int R, int64_t R_batch, int waves_a,
 }
 
 // Workgroups per restart of the grid schedule's workgroup sweep, or 0 where it does not apply
-// (node-by-node templates, a real state beyond the LDS): about two workgroups a CU over the
-// whole call, each with at least two tasks a wave. `work`: tasks x restarts of the call.
+// (node-by-node templates, an atom without an inline record (its kernel has the register store,
+// without the path through the atom table), a real state beyond the LDS): about two workgroups a
+// CU over the whole call, each with at least two tasks a wave. `work`: tasks x restarts of the
+// call.
 static int grid_slices(const fsmt_xbdd *h, int R, int64_t work, size_t budget, int n_cu) {
     const int64_t tasks = sweep_tasks(h);
     const size_t lds = (size_t)h->n_real * 12;
     if (h->small_max_nodes > 0 || h->n_big > 0 || tasks == 0 || h->n_real == 0 || closed_level(h) < 1 ||
-        h->lds_messages || lds > std::min<size_t>(budget, 60000))
+        h->lds_messages || !h->all_inline || lds > std::min<size_t>(budget, 60000))
         return 0;
     const int64_t ideal = std::max<int64_t>(1, work / (2 * n_cu));   // tasks of one workgroup
     const int64_t s = std::max<int64_t>(1, std::min((tasks + ideal - 1) / ideal, tasks / 32));

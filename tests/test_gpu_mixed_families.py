@@ -1,13 +1,15 @@
 """Instances that mix constraint families, against the oracle at the parity bar: window
 disjunctions beside a long cardinality (a big diagram: the grid schedule's sweeps and the
 level-synchronous pass), beside node-by-node templates, with the LDS message store, and where
-the per-call passes keep the state or the message columns out of a workgroup's LDS."""
+the per-call passes keep the state or the message columns out of a workgroup's LDS; index pairs
+with atoms that have no inline record."""
 import numpy as np
 import pytest
 
 import oracle
 import workloads as W
 from workloads.format import KIND_CARD_LE, KIND_EXPR, KIND_XOR, OP_GE, OP_LE, X_AND, X_OR, Builder, lit
+from workloads.paper_suite import index_differs_program
 
 from gpu_util import T, assert_gradient, assert_objective, assert_unsat, dev, torch
 
@@ -92,3 +94,30 @@ def test_windows_out_of_workgroup_lds(nb, beside, extra, R):
     """States of 180 KB, and message columns that leave a workgroup fewer than four waves."""
     print(f"windows of {nb} Booleans beside {beside or 'nothing'}, {extra} more Booleans, R={R}", flush=True)
     _compare(_windows_and(nb, beside, 130, extra), R, 1.2, 10 + nb)
+
+
+def _table_pairs(n, L, form):
+    """Index pairs whose atoms have no inline record: right-hand sides that float32 does not hold
+    (tenths), or three terms."""
+    rng = np.random.default_rng([94, n, L])
+    b = Builder(n * L, n + 1, real_lo=np.full(n + 1, -2.0), real_hi=np.full(n + 1, 2.0))
+    for j in range(n):
+        for k in range(j + 1, n):
+            s = float(rng.integers(1, 9)) / (10.0 if form == "tenths" else 8.0)
+            more = ([], []) if form == "tenths" else ([n], [0.5])
+            at = [b.atom([u, v] + more[0], [1.0, -1.0] + more[1], OP_GE, s) for u, v in ((j, k), (k, j))]
+            bits = sum(([lit(i * n + j), lit(i * n + k)] for i in range(L)), [])
+            b.add(KIND_EXPR, bits + [lit(a) for a in at], 0, index_differs_program(L, 2))
+    return b.build()
+
+
+@pytest.mark.parametrize("form", ["tenths", "terms"])
+@pytest.mark.parametrize("n,L,R,schedule", [(2, 1, 1, 2), (20, 3, 5, 2), (20, 3, 5, 1), (34, 10, 65, 2)])
+def test_index_pairs_through_the_atom_table(form, n, L, R, schedule):
+    p = _table_pairs(n, L, form)
+    print(f"index pairs of {n} items, {L} bits, {form}, R={R}, schedule {schedule}", flush=True)
+    info = _compare(p, R, 1.5, n + L)
+    assert info["n_pair"] == p.n_cons
+    h, a0, b0, st = _one_step(p, R, 1.5, 0.5, 0.1, 95, schedule=schedule)
+    _assert_step(p, a0, b0, st, 1.5, 0.5, 0.1)
+    h.free()
