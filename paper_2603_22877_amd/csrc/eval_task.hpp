@@ -739,9 +739,10 @@ __device__ __forceinline__ GdInfo load_gd(cptr<GdInfo> p) {
     return g;
 }
 
-// Literal probability of an atom from q.b already formed (lin), as atom_literal but with the
-// derivative's scale in FP32: p = erfc(u)/2, u = kappa scale (lin - rhs) (FP64 product,
-// rounded once), dp/dz = -kappa scale/sqrt(pi) e^{-u^2}.
+// Literal probability of an atom from q.b already formed (lin), as atom_literal but by default
+// with the derivative's scale in FP32 (kWide: in FP64, rounded once): p = erfc(u)/2,
+// u = kappa scale (lin - rhs) (FP64 product, rounded once), dp/dz = -kappa scale/sqrt(pi) e^{-u^2}.
+template <bool kWide = false>
 __device__ __forceinline__ void gd_atom(double lin, float rhs, float scale, bool strict, double kappa, bool hard,
                                         float &p, float &q, float &d) {
 #pragma clang fp contract(off)
@@ -760,7 +761,7 @@ __device__ __forceinline__ void gd_atom(double lin, float rhs, float scale, bool
         const float e = half_erfc(fabsf(u), emu2);
         p = (u >= 0.0f) ? e : 1.0f - e;
         q = (u >= 0.0f) ? 1.0f - e : e;
-        d = -((float)ks * 0.56418958354775628695f) * emu2;
+        d = -(kWide ? (float)(ks * 0.56418958354775628695) : (float)ks * 0.56418958354775628695f) * emu2;
     }
 }
 
@@ -1000,7 +1001,7 @@ __device__ __forceinline__ float window_eval(const TabView &T, const TaskCtx &t,
             }
         }
         float p, q;
-        gd_atom(lin, a.rhs, a.scale, (a.flags & 1u) != 0, kappa, hard, p, q, d);
+        gd_atom<true>(lin, a.rhs, a.scale, (a.flags & 1u) != 0, kappa, hard, p, q, d);
         pass = ng ? q : p;
         fail = ng ? p : q;
         d = ng ? -d : d;

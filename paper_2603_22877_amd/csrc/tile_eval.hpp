@@ -61,7 +61,7 @@ __device__ __forceinline__ float tile_run(const TabView &T, const TileSet &S, co
     const int ri = lane >> 3, cj = lane & 7;
     const int L = LM ? S.L : 0;
     const double ks = kappa * (double)S.scale;
-    const float kd = hard ? 0.0f : (float)ks * 0.56418958354775628695f;   // dl/dz = kd e^{-u^2}
+    const float kd = hard ? 0.0f : (float)(ks * 0.56418958354775628695);   // dl/dz = kd e^{-u^2}
     const cptr<uint32_t> rc = T.tile_rc + S.tile0;
     const cptr<int32_t> con = T.tile_con + (int64_t)S.tile0 * 64 + lane;
     auto tile_of = [&](int t) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)rc[t]); };
@@ -265,7 +265,7 @@ __device__ __forceinline__ float cell_run(const TabView &T, const TileSet &S, co
     if (t0 >= t1) return 0.0f;
     const int ri = lane >> 3, cj = lane & 7;
     const double ks = kappa * (double)S.scale;
-    const float kd = hard ? 0.0f : (float)ks * 0.56418958354775628695f;
+    const float kd = hard ? 0.0f : (float)(ks * 0.56418958354775628695);
     const cptr<uint32_t> rc = T.tile_rc + S.tile0;
     const cptr<int32_t> con = T.tile_con + (int64_t)S.tile0 * 64 + lane;
     const cptr<int32_t> aux = T.tile_cell + (int64_t)S.cell0 * 128 + lane;
