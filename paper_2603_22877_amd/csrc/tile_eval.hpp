@@ -171,12 +171,13 @@ __device__ __forceinline__ float tile_run(const TabView &T, const TileSet &S, co
             F = SR * SC;
             if constexpr (kGrad) {
                 const float wr = w0 * SC, wcl = w0 * SR;
-                const float A0 = wr * qr * kd, A1 = wr * pr * kd, B0 = wcl * qc * kd, B1 = wcl * pc * kd;
+                const float A0 = wr * qr, A1 = wr * pr, B0 = wcl * qc, B1 = wcl * pc;
+                // the scale last: a weight times a large kappa would overflow where e^{-u^2} is 0
 #pragma unroll
                 for (int d = 0; d < 2; ++d) {
                     const int o = 1 - d;
-                    gx[d] = (A0 * lr[0][o]) * mr[0][d] + (A1 * lr[1][o]) * mr[1][d] -
-                            ((B0 * lc[0][o]) * mc[0][d] + (B1 * lc[1][o]) * mc[1][d]);
+                    gx[d] = kd * ((A0 * lr[0][o]) * mr[0][d] + (A1 * lr[1][o]) * mr[1][d] -
+                                  ((B0 * lc[0][o]) * mc[0][d] + (B1 * lc[1][o]) * mc[1][d]));
                     gx[d] = valid ? gx[d] : 0.0f;
                     gc[d] -= gx[d];
                 }
@@ -215,14 +216,14 @@ __device__ __forceinline__ float tile_run(const TabView &T, const TileSet &S, co
                     gcb[i] += valid ? rest * rb[i] : 0.0f;
                     pre *= e[i];
                 }
-                const float wk = w0 * suf[0] * kd;
+                const float wk = w0 * suf[0];
                 if constexpr (D == 1) {
-                    gx[0] = (wk * lc[0][0]) * mr[0][0] - (wk * lr[0][0]) * mc[0][0];
+                    gx[0] = kd * ((wk * lc[0][0]) * mr[0][0] - (wk * lr[0][0]) * mc[0][0]);
                 } else {
 #pragma unroll
                     for (int d = 0; d < 2; ++d) {
                         const float other = wk * (lr[0][1 - d] * lc[0][1 - d]);
-                        gx[d] = (other * lc[0][d]) * mr[0][d] - (other * lr[0][d]) * mc[0][d];
+                        gx[d] = kd * ((other * lc[0][d]) * mr[0][d] - (other * lr[0][d]) * mc[0][d]);
                     }
                 }
 #pragma unroll
@@ -317,7 +318,7 @@ __device__ __forceinline__ float cell_run(const TabView &T, const TileSet &S, co
         const float fr = nr ? p : q, fc = nc ? p : q;   // P[literal False]
         const float Fr = fr * lr, Fc = fc * lc;
         if constexpr (kGrad) {
-            float gx = (hr ? wr0 * fr * kd * mr : 0.0f) - (hc ? wc0 * fc * kd * mc : 0.0f);
+            float gx = kd * ((hr ? wr0 * fr * mr : 0.0f) - (hc ? wc0 * fc * mc : 0.0f));
             gc -= gx;
             gx += dpp_of<kDppXor1>(gx);
             gx += dpp_of<kDppXor2>(gx);

@@ -1,9 +1,12 @@
 """The scale kappa / (sqrt(2 pi) |q|) of an atom's derivative, at points where every other factor
 of the gradient is exact in float32: an atom at z = 0 (e^{-u^2} = 1) among literals whose
-probabilities are 0 or 1. The gradient is then the scale itself, rounded once from 64 bits."""
+probabilities are 0 or 1. The gradient is then the scale itself, rounded once from 64 bits.
+And at scales whose product with a weight exceeds float32, where e^{-u^2} is 0."""
 import numpy as np
 import pytest
 
+import oracle
+import workloads as W
 from workloads.format import KIND_EXPR, OP_LE, X_AND, X_OR, Builder, lit
 from workloads.paper_suite import index_differs_program
 
@@ -11,6 +14,7 @@ from gpu_util import T, dev, torch
 
 pytestmark = pytest.mark.gpu
 fsmt = pytest.importorskip("paper_2603_22877_amd")
+from test_gpu_tiles import _clause_pairs, _index_pairs  # noqa: E402
 
 KAPPAS = np.random.default_rng(96).uniform(0.05, 40.0, 64)
 
@@ -66,3 +70,21 @@ def test_windows():
     for kappa in KAPPAS:
         gb = _gradient_b(p, a, y, kappa)
         assert gb[0] == _scale(kappa) and gb[1] == -_scale(kappa), (kappa, gb, _scale(kappa))
+
+
+@pytest.mark.parametrize("make", ["rect", "bits1", "bits2", "clauses"])
+def test_weight_times_scale_beyond_float32(make):
+    """kappa 1e30 and weights of 1e10: no atom is near its bound, so the gradient in b is 0 and the
+    Booleans' is that of the indicator."""
+    p = {"rect": lambda: W.make_placement(40, W.seed_seq(97), fill=0.3, max_side=5), "bits1": lambda: _index_pairs(33, 5, 1, 6),
+         "bits2": lambda: _index_pairs(33, 9, 2, 7), "clauses": lambda: _clause_pairs(40, 3, 8)}[make]()
+    a, b = W.initial_points(p, 3, 98)
+    w = np.full((3, p.n_cons), 1e10, np.float32)
+    h = fsmt.xbdd_compile(p)
+    ga, gb, obj = torch.zeros(3, p.n_bool, device=dev()), torch.zeros(3, p.n_real, device=dev()), torch.zeros(3, device=dev())
+    fsmt.cop_backward(h, T(a), T(b), 1e30, T(w), obj, ga, gb)
+    h.free()
+    o = oracle.objective(p, a, b, 1e30, w=w, per_constraint=False)
+    np.testing.assert_array_equal(gb.cpu().numpy(), np.zeros_like(b))
+    np.testing.assert_allclose(ga.cpu().numpy(), o["grad_a"], rtol=1e-5, atol=4e-7 * o["absg_a"].max())
+    np.testing.assert_allclose(obj.cpu().numpy(), o["U"], rtol=1e-5)
