@@ -579,7 +579,7 @@ fsmt_status solve_impl(const fsmt_xbdd *const *insts, int32_t n_inst, const fsmt
         const size_t off_flg = off_obj + (sizeof(float) * total_r + 255) / 256 * 256;
         const size_t off_gsq = off_flg + (sizeof(int32_t) * gi.size() + 255) / 256 * 256;
         const size_t off_ws = off_gsq + (sizeof(float) * total_r + 255) / 256 * 256;
-        const size_t off_grd = off_ws + (sizeof(float) * total_r + 255) / 256 * 256;
+        const size_t off_grd = off_ws + (sizeof(float) * (size_t)checks + 255) / 256 * 256;
         const size_t off_row = off_grd + (sizeof(float) * (size_t)scratch_floats + 255) / 256 * 256;
         const size_t total = off_row + sizeof(float) * (size_t)row_floats;
         void *buf = nullptr;
@@ -601,7 +601,7 @@ fsmt_status solve_impl(const fsmt_xbdd *const *insts, int32_t n_inst, const fsmt
             S.obj_acc = (float *)(base + off_obj);
             S.stop_flags = (int32_t *)(base + off_flg);
             S.gsq_acc = (float *)(base + off_gsq);
-            S.ws_acc = (float *)(base + off_ws);
+            S.ws_part = (float *)(base + off_ws);
             S.rows = (float *)(base + off_row);
             S.total_r = total_r;
             S.n_levels = O.n_levels;

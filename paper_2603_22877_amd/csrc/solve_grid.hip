@@ -52,7 +52,6 @@ __global__ void grid_begin_kernel(const GridInst *insts, int n_inst, GridShared 
     S.stepping[g] = act;
     S.obj_acc[g] = 0.0f;
     S.gsq_acc[g] = 0.0f;
-    S.ws_acc[g] = 0.0f;
     if (act) {
         I.n_unsat[r] = 0;
         if (I.verdict[r] < 0) I.verdict[r] = 0;   // an earlier call gave up: resume as not SAT
@@ -338,8 +337,8 @@ __device__ __forceinline__ GroupOf group_of(const GridInst *insts, int n_inst) {
     return GroupOf{ii, (int)(lb / groups), (int)(lb % groups) * 256 + (int)threadIdx.x};
 }
 
-// Exact check and ERWA update of the history and the weights, whose sum per restart goes to
-// ws_acc (normalized by grid_scale_kernel).
+// Exact check and ERWA update of the history and the weights; each block's sum of its weights
+// goes to ws_part (normalized by grid_scale_kernel).
 __global__ void __launch_bounds__(256) grid_check_kernel(const GridInst *insts, int n_inst, GridShared S) {
     const int lane = threadIdx.x & 63;
     const GroupOf G = group_of(insts, n_inst);
@@ -373,17 +372,22 @@ __global__ void __launch_bounds__(256) grid_check_kernel(const GridInst *insts, 
     }
     if (S.normalize) {
         const float ws = block_sum(wv);
-        if (threadIdx.x == 0) atomic_add_f32(S.ws_acc + I.rbase + r, ws);
+        if (threadIdx.x == 0) S.ws_part[blockIdx.x] = ws;
     }
 }
 
-// Weights normalized to sum n_cons after an update.
+// Weights normalized to sum n_cons after an update. Every block adds its restart's block sums in
+// the same fixed order (no atomics: equal check bits give equal weights in every run).
 __global__ void __launch_bounds__(256) grid_scale_kernel(const GridInst *insts, int n_inst, GridShared S) {
     const GroupOf G = group_of(insts, n_inst);
     const GridInst &I = insts[G.ii];
-    const int C = I.T.n_cons;
-    if (!S.active[I.rbase + G.r] || ((I.level_done[G.r] + 1) % S.tau) != 0 || G.c >= C) return;
-    I.w[(int64_t)G.r * C + G.c] *= (float)C / S.ws_acc[I.rbase + G.r];
+    const int C = I.T.n_cons, groups = (C + 255) / 256;
+    if (!S.active[I.rbase + G.r] || ((I.level_done[G.r] + 1) % S.tau) != 0) return;   // uniform
+    const float *part = S.ws_part + I.check_base + (int64_t)G.r * groups;
+    float ws = 0.0f;
+    for (int q = threadIdx.x; q < groups; q += 256) ws += part[q];
+    ws = block_sum(ws);
+    if (G.c < C) I.w[(int64_t)G.r * C + G.c] *= (float)C / ws;
 }
 
 // Level counter and verdict, one thread per restart.

@@ -44,7 +44,7 @@ struct GridShared {
     int32_t level_floats;           // floats of one wave's rows there
     int64_t tile_tasks;             // (restart, chunk of tiles) tasks over all instances
     float *gsq_acc;                 // [total_r] gradient map of the Booleans that grid_wg_kernel updates
-    float *ws_acc;                  // [total_r] sum of the updated weights
+    float *ws_part;                 // [check blocks] sum of a block's updated weights
     float *rows;                    // per (restart, slice): gradient of the real variables
 };
 
