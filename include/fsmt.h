@@ -208,7 +208,8 @@ fsmt_status cop_forward(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, double kap
  * chain rule dp/da = -1/2 and dp/db_j = -kappa q_j exp(-u^2) / (sqrt(2 pi) |q|)
  * (Supplementary Note 6). grad_a [R][n_bool], grad_b [R][n_real] receive grad U; obj
  * (optional, NULL to skip) receives U. Without FSMT_ACCUMULATE the outputs are zeroed
- * first. Gradient sums are taken in no fixed order, so the last bits vary between runs. On
+ * first; with it they are added with atomics, so calls on several streams may accumulate into one
+ * buffer. Gradient sums are taken in no fixed order, so the last bits vary between runs. On
  * instances of at least 8 x 64 constraints per compute unit the call takes stream-ordered work
  * memory (hipMallocAsync / hipFreeAsync on `stream`): a gradient row per workgroup where a
  * restart's state fits the LDS (device atomics instead when the allocation fails or the stream

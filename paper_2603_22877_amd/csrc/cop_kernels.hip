@@ -114,8 +114,8 @@ __global__ void __launch_bounds__(256) cop_tile_kernel(CopArgs A, int chunks) {
 // LdsScatter) in LDS; `slices` workgroups share a restart's sweep (slice-minor block numbers,
 // so with a multiple of 8 slices the workgroups of one slice read the same tables on one XCD).
 // The outputs leave the workgroup in one of three ways:
-//   kStore: one slice; stored (or added, with accumulate) into the caller's views: the whole
-//           call is this one launch;
+//   kStore: one slice, no accumulation; stored into the caller's views: the whole call is this one
+//           launch;
 //   kAdd  : added into the zeroed (or accumulating) views with device atomics, one per
 //           variable and slice;
 //   kRows : written as the slice's row of `part` (objective: opart), summed by sum_rows_kernel.
@@ -150,7 +150,7 @@ __device__ __forceinline__ void wg_load_point(const View &a, const View &b, int 
 // the three ways.
 template <bool kGrad, class G>
 __device__ __forceinline__ void wg_store(float oacc, int r, int n, int nm, const G *ga, float *obj, const View &va,
-                                         const View &vb, int mode, int accumulate, float *part, double *opart) {
+                                         const View &vb, int mode, float *part, double *opart) {
     __shared__ double part_o[16];
     const int lane = threadIdx.x & 63, wib = wave_id(), wpb = blockDim.x >> 6;
     double o = oacc;
@@ -161,7 +161,7 @@ __device__ __forceinline__ void wg_store(float oacc, int r, int n, int nm, const
         double t = 0.0;
         for (int q = 0; q < wpb; ++q) t += part_o[q];
         if (mode == kRows) opart[blockIdx.x] = t;
-        else if (obj && mode == kStore) obj[r] = accumulate ? obj[r] + (float)t : (float)t;
+        else if (obj && mode == kStore) obj[r] = (float)t;
         else if (obj) atomic_add_f32(obj + r, (float)t);
     }
     if constexpr (kGrad) {
@@ -175,7 +175,7 @@ __device__ __forceinline__ void wg_store(float oacc, int r, int n, int nm, const
                 if (mode == kAdd) {
                     if (g != 0.0f) atomic_add_f32(&dst, g);
                 } else {
-                    dst = accumulate ? dst + g : g;
+                    dst = g;
                 }
             }
         }
@@ -219,7 +219,7 @@ __global__ void __launch_bounds__(1024) cop_wg_kernel(CopArgs A, int slices, int
         oacc += wc * unsat;
     }
     oacc += tile_sweep<kCF, kGrad>(A.T, st, sc, r, A.kappa, hard, id, n_waves, wload, fout, lane);
-    wg_store<kGrad>(oacc, r, n, nm, ga, A.obj, A.ga, A.gb, mode, accumulate, part, opart);
+    wg_store<kGrad>(oacc, r, n, nm, ga, A.obj, A.ga, A.gb, mode, part, opart);
 }
 
 // Restart r = blockIdx.y: its slices' rows added and stored into (or added to) the caller's
@@ -251,13 +251,17 @@ __global__ void __launch_bounds__(1024) sum_rows_kernel(const float *part, const
         float t = 0.0f;
         for (int q = 0; q < 16; ++q) t += red[q][c];
         gref<float> dst = e < n ? ga.at(r, e) : gb.at(r, e - n);
-        if (accumulate) dst += t; else dst = t;
+        if (!accumulate) dst = t;
+        else if (t != 0.0f) atomic_add_f32(&dst, t);
     }
     if (obj && blockIdx.x == 0 && threadIdx.x < 64) {
         double t = 0.0;
         for (int w = threadIdx.x; w < slices; w += 64) t += opart[(int64_t)r * slices + w];
         for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
-        if (threadIdx.x == 0) obj[r] = accumulate ? obj[r] + (float)t : (float)t;
+        if (threadIdx.x == 0) {
+            if (accumulate) atomic_add_f32(obj + r, (float)t);
+            else obj[r] = (float)t;
+        }
     }
 }
 
@@ -314,7 +318,7 @@ __global__ void __launch_bounds__(256) cop_level_kernel(LevelArgs A) {
 // otherwise adds into its literals' gradients with device atomics on as many lines (random
 // hybrid 500 x 100 points: 184 us a call).
 template <bool kGrad>
-__global__ void __launch_bounds__(768) cop_big_wg_kernel(LevelArgs A, int slices, int mode, int accumulate) {
+__global__ void __launch_bounds__(768) cop_big_wg_kernel(LevelArgs A, int slices, int mode) {
     extern __shared__ __align__(16) float lds[];
     const int lane = threadIdx.x & 63, wib = wave_id(), wpb = blockDim.x >> 6;
     const int n = A.T.n_bool, m = A.T.n_real, nm = n + m;
@@ -342,7 +346,7 @@ __global__ void __launch_bounds__(768) cop_big_wg_kernel(LevelArgs A, int slices
             oacc += wc * unsat;
         }
     }
-    wg_store<kGrad>(oacc, r, n, nm, ga, A.obj, A.ga, A.gb, mode, accumulate, nullptr, nullptr);
+    wg_store<kGrad>(oacc, r, n, nm, ga, A.obj, A.ga, A.gb, mode, nullptr, nullptr);
 }
 
 // ------------------------------------------------------------------ small kernels
@@ -353,7 +357,8 @@ __global__ void unstage_kernel(View out, const float *stage, int R, int cols, in
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
         const int v = (int)(e / R), r = (int)(e - (int64_t)v * R);
         const float g = stage[e];
-        if (accumulate) out.at(r, v) += g; else out.at(r, v) = g;
+        if (!accumulate) out.at(r, v) = g;
+        else if (g != 0.0f) atomic_add_f32(&out.at(r, v), g);
     }
 }
 
@@ -790,6 +795,11 @@ static fsmt_status cop_launch(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, doub
         clear_error();
         big = WgGeom{};   // the level kernel takes them
     }
+    // accumulation adds with atomics in every path: calls on several streams that accumulate into
+    // one buffer add up
+    const int accumulate = flags & FSMT_ACCUMULATE;
+    if (accumulate && wg.mode == kStore) wg.mode = kAdd;
+    if (accumulate && big.mode == kStore) big.mode = kAdd;
     const bool large = sweep_tasks(h) >= (int64_t)8 * n_cu;
     const bool stage = !wg.slices && !big.slices && grad && large && R >= 4 && R <= 64 && (int64_t)(n + m) * R > 0 &&
                        !(ga.stride_r == 1 && gb.stride_r == 1);
@@ -820,7 +830,6 @@ static fsmt_status cop_launch(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, doub
         if ((rc = fill_f32(sg.p, (int64_t)(n + m) * R, 0.0f, st))) return rc;
     }
     float *const sbuf = sg.p;
-    const int accumulate = flags & FSMT_ACCUMULATE;
     // the workgroups store the outputs
     const bool whole = (wg.slices && wg.mode != kAdd) || (big.slices && big.mode == kStore);
     const bool zero_free = wg.mixed && grad && h->n_free > 0;   // added with atomics
@@ -925,7 +934,7 @@ static fsmt_status cop_launch(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, doub
         L.wave_floats = (int32_t)(level_wave_bytes / sizeof(float));
         L.chunk = level_chunk((int64_t)h->n_big * R, n_cu);
         if (big.slices) {
-            void *args[] = {(void *)&L, (void *)&big.slices, (void *)&big.mode, (void *)&accumulate};
+            void *args[] = {(void *)&L, (void *)&big.slices, (void *)&big.mode};
             const hipError_t le = hipLaunchKernel(big_wg_fn(grad), dim3((unsigned)(R * big.slices)), dim3(64 * big.waves), args,
                                                   big.lds, st);
             if (le != hipSuccess) return set_error(FSMT_EHIP, "cop kernel (big diagrams): %s", hipGetErrorString(le));
@@ -943,9 +952,9 @@ static fsmt_status cop_launch(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, doub
     }
     if (stage) {
         hipLaunchKernelGGL(unstage_kernel, dim3(blocks_for((int64_t)R * n, 256)), dim3(256), 0, st, View::of(ga),
-                           (const float *)sbuf, R, n, flags & FSMT_ACCUMULATE);
+                           (const float *)sbuf, R, n, accumulate);
         hipLaunchKernelGGL(unstage_kernel, dim3(blocks_for((int64_t)R * m, 256)), dim3(256), 0, st, View::of(gb),
-                           (const float *)(sbuf + (size_t)n * R), R, m, flags & FSMT_ACCUMULATE);
+                           (const float *)(sbuf + (size_t)n * R), R, m, accumulate);
         if ((rc = launch_status("gradient unstage"))) return rc;
     }
     return FSMT_OK;

@@ -137,8 +137,10 @@ struct GlobalScatter {
     __device__ __forceinline__ void add(int r, bool real, int i, float g) const {
         if (g != 0.0f) atomic_add_f32(real ? &gb.at(r, i) : &ga.at(r, i), g);
     }
-    // a cell's own Boolean: no other lane adds to it
-    __device__ __forceinline__ void cell(int r, int i, float, float g) const { ga.at(r, i) += g; }
+    // a cell's own Boolean: no other lane of the call adds to it
+    __device__ __forceinline__ void cell(int r, int i, float, float g) const {
+        if (g != 0.0f) atomic_add_f32(&ga.at(r, i), g);
+    }
 };
 // LDS: the fused solver's gradient lives in LDS and its atomics stay on the CU. G is double
 // where the state leaves room for it: a wave-wide LDS add of 64 distinct addresses takes 9
@@ -187,8 +189,8 @@ struct MixedScatter {
         else atomic_add_f32(&ga.at(r, i), g);
     }
     __device__ __forceinline__ void cell(int r, int i, float, float g) const {
-        gref<float> dst = ga.at(r, i);
-        dst = accumulate ? dst + g : g;
+        if (!accumulate) ga.at(r, i) = g;
+        else if (g != 0.0f) atomic_add_f32(&ga.at(r, i), g);
     }
 };
 
