@@ -583,10 +583,29 @@ static void launch_cop(int cf, int msg, dim3 g, dim3 bl, size_t lds, hipStream_t
     else launch_cop_v<kGrad, 4>(msg, g, bl, lds, st, A);
 }
 
-fsmt_status allow_lds(const void *fn, size_t bytes) {
-    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess) return FSMT_OK;
-    (void)hipGetLastError();
-    return set_error(FSMT_ELIMIT, "a kernel's LDS (%zu B) exceeds the device's", bytes);
+size_t lds_opt_in(const std::vector<const void *> &fns, int device) {
+    int v = 0;
+    size_t b = 65536, stat = 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, device) == hipSuccess && (size_t)v > b) b = (size_t)v;
+    else (void)hipGetLastError();
+    for (const void *f : fns) {
+        hipFuncAttributes fa{};
+        if (hipFuncGetAttributes(&fa, f) == hipSuccess) stat = std::max(stat, (size_t)fa.sharedSizeBytes);
+        else (void)hipGetLastError();
+    }
+    bool ok = true;
+    for (const void *f : fns)
+        if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(b - stat)) != hipSuccess) {
+            (void)hipGetLastError();
+            ok = false;
+        }
+    return (ok ? b : 65536) - stat;
+}
+
+size_t LdsBudget::of(int device, std::vector<const void *> (*fns)()) {
+    if (device < 0 || device >= kMaxDevices) return lds_opt_in(fns(), device);
+    std::call_once(once[device], [&] { bytes[device] = lds_opt_in(fns(), device); });
+    return bytes[device];
 }
 
 static int blocks_for(int64_t n, int threads, int cap = 4096) {
@@ -627,36 +646,32 @@ static const void *cop_wg_fn(bool grad, int msg, int cf, bool wide, bool mixed =
                      : cop_wg_fn_cf<4>(grad, msg, wide, mixed);
 }
 
-// Dynamic LDS the one-restart-per-workgroup kernels may take: the device's per-block maximum,
-// opted into once for every instantiation, less their static LDS (64 KB in all if the device
-// reports no more).
-static size_t lds_wg_budget() {
-    static size_t budget = 0;
-    static std::once_flag once;
-    std::call_once(once, [] {
-        int dev = 0, v = 0;
-        size_t b = 65536, stat = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && (size_t)v > b)
-            b = (size_t)v;
-        std::vector<const void *> fns;
-        for (int grad = 0; grad < 2; ++grad)
-            for (int msg : {kMsgSmall, kMsgLds})
-                for (int cf = 0; cf < 5; ++cf)
-                    for (int wide = 0; wide < 3; ++wide) fns.push_back(cop_wg_fn(grad != 0, msg, cf, wide == 1, wide == 2));
-        for (const void *f : fns) {
-            hipFuncAttributes fa{};
-            if (hipFuncGetAttributes(&fa, f) == hipSuccess) stat = std::max(stat, (size_t)fa.sharedSizeBytes);
-            else (void)hipGetLastError();
-        }
-        for (const void *f : fns)
-            if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(b - stat)) != hipSuccess) {
-                (void)hipGetLastError();
-                b = 65536;
-            }
-        budget = b - stat;
-    });
-    return budget;
+static const void *level_kernel_fn(bool grad) {
+    return grad ? (const void *)cop_level_kernel<true> : (const void *)cop_level_kernel<false>;
+}
+static const void *big_wg_fn(bool grad) {
+    return grad ? (const void *)cop_big_wg_kernel<true> : (const void *)cop_big_wg_kernel<false>;
+}
+
+// Dynamic LDS the one-restart-per-workgroup kernels may take, and the kernels of big diagrams.
+static std::vector<const void *> cop_wg_fns() {
+    std::vector<const void *> fns;
+    for (int grad = 0; grad < 2; ++grad)
+        for (int msg : {kMsgSmall, kMsgLds})
+            for (int cf = 0; cf < 5; ++cf)
+                for (int wide = 0; wide < 3; ++wide) fns.push_back(cop_wg_fn(grad != 0, msg, cf, wide == 1, wide == 2));
+    return fns;
+}
+static std::vector<const void *> big_fns() {
+    return {level_kernel_fn(false), level_kernel_fn(true), big_wg_fn(false), big_wg_fn(true)};
+}
+static size_t lds_wg_budget(int device) {
+    static LdsBudget B;
+    return B.of(device, cop_wg_fns);
+}
+static size_t lds_big_budget(int device) {
+    static LdsBudget B;
+    return B.of(device, big_fns);
 }
 
 // Geometry of the one-restart-per-workgroup kernel, or slices = 0 where it does not apply: a
@@ -669,10 +684,11 @@ struct WgGeom {
 static WgGeom big_geom(const fsmt_xbdd *h, int R, bool grad, size_t level_wave_bytes, int n_cu) {
     WgGeom G;
     const size_t nm = (size_t)h->n_bool + h->n_real, state = (nm * (grad ? 12 : 4) + 31) / 16 * 16;
-    const size_t cap = 160 * 1024 - 1024;   // less the static sums
     // with few restarts the level kernel spreads the constraints over more workgroups (random
     // hybrid 100 at 7 points: 17 us a call against 39 here)
-    if (R < 32 || h->n_big == 0 || h->n_big != h->n_cons || nm == 0 || state + 4 * level_wave_bytes > cap) return G;
+    if (R < 32 || h->n_big == 0 || h->n_big != h->n_cons || nm == 0) return G;
+    const size_t cap = lds_big_budget(h->device);
+    if (state + 4 * level_wave_bytes > cap) return G;
     G.waves = (int)std::min<size_t>(12, (cap - state) / level_wave_bytes);
     // a wave has about four constraints where the restarts do not fill the device
     const int64_t s = std::min<int64_t>(n_cu / std::max(1, R), h->n_big / (4 * G.waves));
@@ -685,7 +701,7 @@ static WgGeom wg_geom(const fsmt_xbdd *h, int R, bool grad, int msg, size_t wave
     WgGeom G;
     const int64_t tasks = sweep_tasks(h), nm = (int64_t)h->n_bool + h->n_real;
     if (tasks == 0 || nm == 0 || h->n_big == h->n_cons || (msg != kMsgSmall && msg != kMsgLds)) return G;
-    const size_t cap = lds_wg_budget();
+    const size_t cap = lds_wg_budget(h->device);
     // waves of a workgroup: one per task up to 16, fewer where the message columns need the LDS
     auto waves_of = [&](size_t state) -> int {
         if (state + wave_bytes > cap) return 0;
@@ -724,14 +740,6 @@ static WgGeom wg_geom(const fsmt_xbdd *h, int R, bool grad, int msg, size_t wave
     G.mode = G.slices == 1 ? kStore : (grad && large) ? kRows : kAdd;
     G.lds = (state + (size_t)G.waves * wave_bytes + 15) / 16 * 16;
     return G;
-}
-
-static const void *level_kernel_fn(bool grad) {
-    return grad ? (const void *)cop_level_kernel<true> : (const void *)cop_level_kernel<false>;
-}
-
-static const void *big_wg_fn(bool grad) {
-    return grad ? (const void *)cop_big_wg_kernel<true> : (const void *)cop_big_wg_kernel<false>;
 }
 
 static fsmt_status cop_launch(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, double kappa, fsmt_view w, float *obj,
@@ -791,10 +799,6 @@ static fsmt_status cop_launch(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, doub
         else if (cap != hipStreamCaptureStatusNone) wg.mode = kAdd;
     }
     WgGeom big = big_geom(h, R, grad, level_wave_bytes, n_cu);
-    if (big.slices && big.lds > 65536 && allow_lds(big_wg_fn(grad), big.lds) != FSMT_OK) {
-        clear_error();
-        big = WgGeom{};   // the level kernel takes them
-    }
     // accumulation adds with atomics in every path: calls on several streams that accumulate into
     // one buffer add up
     const int accumulate = flags & FSMT_ACCUMULATE;
@@ -941,7 +945,8 @@ static fsmt_status cop_launch(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, doub
             return FSMT_OK;
         }
         const int lwpb = (int)std::max<size_t>(1, std::min<size_t>(4, 65536 / level_wave_bytes));
-        if (level_wave_bytes > 65536 && (rc = allow_lds(level_kernel_fn(grad), level_wave_bytes))) return rc;
+        if (level_wave_bytes > 65536 && level_wave_bytes > lds_big_budget(h->device))
+            return set_error(FSMT_ELIMIT, "a big diagram's rows (%zu B) exceed the device's LDS", level_wave_bytes);
         const int64_t ltasks = (int64_t)h->n_big * ((R + L.chunk - 1) / L.chunk);
         const int lblocks = (int)std::min<int64_t>((ltasks + lwpb - 1) / lwpb, (int64_t)256 * 16);
         if (grad)

@@ -2,6 +2,9 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <mutex>
+#include <vector>
+
 #include "fsmt_internal.hpp"
 
 namespace fsmt {
@@ -359,8 +362,17 @@ fsmt_status fill_f32(float *p, int64_t n, float value, hipStream_t st);
 fsmt_status fill_i32(int32_t *p, int64_t n, int32_t value, hipStream_t st);
 fsmt_status check_device_ptr(const void *p, int device, const char *name);
 fsmt_status select_device(const fsmt_xbdd *h);
-// Lets kernel fn take `bytes` of dynamic LDS (past the default 64 KB).
-fsmt_status allow_lds(const void *fn, size_t bytes);
+// Lets the kernels take the device's whole LDS (its per-block maximum less their static LDS) as
+// dynamic LDS and returns that size; 64 KB less the static LDS where the device refuses.
+size_t lds_opt_in(const std::vector<const void *> &fns, int device);
+// The same once per device (the attribute belongs to a kernel on a device, and setting it to a
+// call's own need would lower it under another thread that is about to launch).
+constexpr int kMaxDevices = 64;
+struct LdsBudget {
+    std::once_flag once[kMaxDevices];
+    size_t bytes[kMaxDevices] = {};
+    size_t of(int device, std::vector<const void *> (*fns)());
+};
 HalfSpaces halfspaces_of(const fsmt_xbdd *h);
 
 }  // namespace fsmt

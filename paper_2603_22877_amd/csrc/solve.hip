@@ -38,38 +38,18 @@ static const void *solve_kernel_fn(int msg, bool cl, int cf, bool wide) {
                      : solve_kernel_cf4(msg, cl, wide);
 }
 
-// Dynamic LDS a persistent workgroup may take: the device's per-block maximum (opted into
-// for every solver kernel) less the largest static LDS of those kernels (the block
-// reductions' partial sums).
-static int lds_budget_bytes() {
-    static int budget = -1;
-    if (budget < 0) {
-        int b = 65536;
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) == hipSuccess &&
-            hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) == hipSuccess && v > b)
-            b = v;
-        std::vector<const void *> fns;
-        for (int msg : {kMsgLds, kMsgSmall, kMsgMedium, kMsgLarge})
-            for (int cl = 0; cl < 2; ++cl)
-                for (int cf = 0; cf < 5; ++cf)
-                    for (int wide = 0; wide < 2; ++wide) fns.push_back(solve_kernel_fn(msg, cl != 0, cf, wide != 0));
-        size_t static_lds = 0;
-        for (const void *f : fns) {
-            hipFuncAttributes fa{};
-            if (hipFuncGetAttributes(&fa, f) == hipSuccess) static_lds = std::max(static_lds, (size_t)fa.sharedSizeBytes);
-            else (void)hipGetLastError();
-        }
-        const int dyn = b - (int)static_lds;
-        for (const void *f : fns) {
-            if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, dyn) != hipSuccess) {
-                (void)hipGetLastError();
-                b = 65536;
-            }
-        }
-        budget = b - (int)static_lds;
-    }
-    return budget;
+// Dynamic LDS a persistent workgroup may take.
+static std::vector<const void *> solve_fns() {
+    std::vector<const void *> fns;
+    for (int msg : {kMsgLds, kMsgSmall, kMsgMedium, kMsgLarge})
+        for (int cl = 0; cl < 2; ++cl)
+            for (int cf = 0; cf < 5; ++cf)
+                for (int wide = 0; wide < 2; ++wide) fns.push_back(solve_kernel_fn(msg, cl != 0, cf, wide != 0));
+    return fns;
+}
+static size_t lds_budget(int device) {
+    static LdsBudget B;
+    return B.of(device, solve_fns);
 }
 
 static int solve_waves(int msg, int cf) {
@@ -87,7 +67,6 @@ static size_t state_floats_of(const fsmt_xbdd *h, bool wide = false) {
 // A stream for the grid part of a mixed batch, a stream to capture level graphs on, the
 // fork/join events, and instantiated level graphs waiting for their last launch to finish
 // before they are destroyed (checked without blocking at the next call).
-constexpr int kMaxDevices = 64;
 struct DeviceRes {
     bool init = false;
     hipStream_t fork = nullptr, cap = nullptr;
@@ -298,7 +277,7 @@ fsmt_status solve_impl(const fsmt_xbdd *const *insts, int32_t n_inst, const fsmt
     mem.cap = fixed_cap;
 
     // ---- schedule choice per instance
-    const size_t budget = (size_t)lds_budget_bytes();
+    const size_t budget = lds_budget(device);
     int n_cu = 256;
     (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, device);
     std::vector<char> use_grid(n_inst, 0);

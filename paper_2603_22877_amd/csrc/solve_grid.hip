@@ -493,6 +493,8 @@ void reap_retired(std::vector<GraphRetired> &list) {
     list.resize(keep);
 }
 
+static std::vector<const void *> level_fns() { return {(const void *)grid_level_kernel}; }
+
 fsmt_status run_grid_schedule(const GridInst *d_insts, int n_inst, const GridShared &S, const GridPlan &P,
                               int n_levels, hipStream_t st, hipStream_t cap, std::vector<GraphRetired> &retired) {
     if (n_levels <= 0 || n_inst == 0) return FSMT_OK;
@@ -500,8 +502,10 @@ fsmt_status run_grid_schedule(const GridInst *d_insts, int n_inst, const GridSha
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     if (P.level_lds > 65536) {
-        const fsmt_status lrc = allow_lds((const void *)grid_level_kernel, P.level_lds);
-        if (lrc) return lrc;
+        static LdsBudget B;
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || P.level_lds > B.of(dev, level_fns))
+            return set_error(FSMT_ELIMIT, "a big diagram's rows (%zu B) exceed the device's LDS", P.level_lds);
     }
     bool use_graph = cap != nullptr && P.use_graph && n_levels > 1;
     if (use_graph && hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) != hipSuccess) use_graph = false;
