@@ -93,20 +93,21 @@ __global__ void __launch_bounds__(256) cop_kernel(CopArgs A) {
 // Tiled constraints of instances whose state does not fit LDS: one wave per (restart, chunk of
 // tiles), the state and the gradient in global memory.
 constexpr int kTileChunk = 32;
+constexpr int64_t kMaxBlocks = 1 << 20;   // of the kernels whose waves loop over their tasks
 template <bool kGrad>
 __global__ void __launch_bounds__(256) cop_tile_kernel(CopArgs A, int chunks) {
-    const int lane = threadIdx.x & 63;
-    const int64_t w = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave_id();
-    const int r = (int)(w / chunks), id = (int)(w - (int64_t)r * chunks);
-    if (r >= A.R) return;
+    const int lane = threadIdx.x & 63, wpb = blockDim.x >> 6;
     const GlobalState st{A.a, A.b};
     const GlobalScatter sc{A.ga, A.gb, 64};
-    auto fout = [&](int c, float F) {
-        if (A.unsat.data) A.unsat.at(r, c) = F;
-    };
-    const float oacc = wave_sum(tile_sweep<3, kGrad>(A.T, st, sc, r, A.kappa, A.hard != 0, id, chunks,
-                                                     [&](int c) -> float { return A.w.at(r, c); }, fout, lane));
-    if (A.obj && lane == 0 && oacc != 0.0f) atomic_add_f32(A.obj + r, oacc);
+    for (int64_t w = (int64_t)blockIdx.x * wpb + wave_id(); w < (int64_t)A.R * chunks; w += (int64_t)gridDim.x * wpb) {
+        const int r = (int)(w / chunks), id = (int)(w - (int64_t)r * chunks);
+        auto fout = [&](int c, float F) {
+            if (A.unsat.data) A.unsat.at(r, c) = F;
+        };
+        const float oacc = wave_sum(tile_sweep<3, kGrad>(A.T, st, sc, r, A.kappa, A.hard != 0, id, chunks,
+                                                         [&](int c) -> float { return A.w.at(r, c); }, fout, lane));
+        if (A.obj && lane == 0 && oacc != 0.0f) atomic_add_f32(A.obj + r, oacc);
+    }
 }
 
 // ------------------------------------------------------------------ one restart per workgroup
@@ -613,6 +614,15 @@ static int blocks_for(int64_t n, int threads, int cap = 4096) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(b, cap));
 }
 
+// Restarts of one launch with a workgroup each: the runtime drops what a grid has past 2^32
+// threads without an error.
+static int rows_per_launch(int R, int threads) { return (int)std::min<int64_t>(R, (int64_t)UINT32_MAX / threads); }
+// Rows r0 .. of a view.
+static View rows_from(View v, int64_t r0) {
+    if (v.data) v.data += r0 * v.sr;
+    return v;
+}
+
 fsmt_status fill_i32(int32_t *p, int64_t n, int32_t value, hipStream_t st) {
     if (!p || n <= 0) return FSMT_OK;
     hipLaunchKernelGGL(fill_i32_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, st, p, n, value);
@@ -892,11 +902,18 @@ static fsmt_status cop_launch(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, doub
     if (wg.slices) {
         double *const opart = rows ? (double *)sbuf : nullptr;
         float *const part = rows ? (float *)(opart + (size_t)R * wg.slices) : nullptr;
-        if ((int64_t)R * wg.slices > INT32_MAX) return set_error(FSMT_ELIMIT, "too many restarts");
-        void *args[] = {(void *)&A, (void *)&wg.slices, (void *)&wg.mode, (void *)&accumulate, (void *)&part, (void *)&opart};
-        const hipError_t le = hipLaunchKernel(cop_wg_fn(grad, msg, cf, wg.wide, wg.mixed), dim3(R * wg.slices), dim3(64 * wg.waves),
-                                              args, wg.lds, st);
-        if (le != hipSuccess) return set_error(FSMT_EHIP, "cop kernel (state in LDS): %s", hipGetErrorString(le));
+        // several slices only below a restart a CU: then one launch has all of them
+        const int rows_max = wg.slices > 1 ? R : rows_per_launch(R, 64 * wg.waves);
+        for (int r0 = 0, nr; r0 < R; r0 += nr) {
+            nr = std::min(R - r0, rows_max);
+            CopArgs B = A;
+            for (View *v : {&B.a, &B.b, &B.w, &B.unsat, &B.ga, &B.gb}) *v = rows_from(*v, r0);
+            if (B.obj) B.obj += r0;
+            void *args[] = {(void *)&B, (void *)&wg.slices, (void *)&wg.mode, (void *)&accumulate, (void *)&part, (void *)&opart};
+            const hipError_t le = hipLaunchKernel(cop_wg_fn(grad, msg, cf, wg.wide, wg.mixed), dim3((unsigned)(nr * wg.slices)),
+                                                  dim3(64 * wg.waves), args, wg.lds, st);
+            if (le != hipSuccess) return set_error(FSMT_EHIP, "cop kernel (state in LDS): %s", hipGetErrorString(le));
+        }
         if (rows) {
             hipLaunchKernelGGL(sum_rows_kernel, dim3((n_row + m + 63) / 64, R), dim3(1024), 0, st, (const float *)part,
                                (const double *)opart, wg.slices, n_row, m, View::of(ga), View::of(gb), obj, accumulate);
@@ -911,7 +928,7 @@ static fsmt_status cop_launch(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, doub
         }
         if (h->n_tiles > 0) {
             const int chunks = (h->n_tiles + kTileChunk - 1) / kTileChunk;
-            const dim3 tg((unsigned)(((int64_t)R * chunks + 3) / 4)), tb(256);
+            const dim3 tg((unsigned)std::min<int64_t>(((int64_t)R * chunks + 3) / 4, kMaxBlocks)), tb(256);
             if (grad) hipLaunchKernelGGL(cop_tile_kernel<true>, tg, tb, 0, st, A, chunks);
             else hipLaunchKernelGGL(cop_tile_kernel<false>, tg, tb, 0, st, A, chunks);
             if ((rc = launch_status("cop tile kernel"))) return rc;
@@ -938,10 +955,17 @@ static fsmt_status cop_launch(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, doub
         L.wave_floats = (int32_t)(level_wave_bytes / sizeof(float));
         L.chunk = level_chunk((int64_t)h->n_big * R, n_cu);
         if (big.slices) {
-            void *args[] = {(void *)&L, (void *)&big.slices, (void *)&big.mode};
-            const hipError_t le = hipLaunchKernel(big_wg_fn(grad), dim3((unsigned)(R * big.slices)), dim3(64 * big.waves), args,
-                                                  big.lds, st);
-            if (le != hipSuccess) return set_error(FSMT_EHIP, "cop kernel (big diagrams): %s", hipGetErrorString(le));
+            const int rows_max = big.slices > 1 ? R : rows_per_launch(R, 64 * big.waves);
+            for (int r0 = 0, nr; r0 < R; r0 += nr) {
+                nr = std::min(R - r0, rows_max);
+                LevelArgs B = L;
+                for (View *v : {&B.a, &B.b, &B.w, &B.unsat, &B.ga, &B.gb}) *v = rows_from(*v, r0);
+                if (B.obj) B.obj += r0;
+                void *args[] = {(void *)&B, (void *)&big.slices, (void *)&big.mode};
+                const hipError_t le = hipLaunchKernel(big_wg_fn(grad), dim3((unsigned)(nr * big.slices)), dim3(64 * big.waves),
+                                                      args, big.lds, st);
+                if (le != hipSuccess) return set_error(FSMT_EHIP, "cop kernel (big diagrams): %s", hipGetErrorString(le));
+            }
             return FSMT_OK;
         }
         const int lwpb = (int)std::max<size_t>(1, std::min<size_t>(4, 65536 / level_wave_bytes));
@@ -1007,10 +1031,16 @@ fsmt_status pgd_step(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, fsmt_view gra
     // as many threads as the swept half-spaces or the variables can use
     const int64_t per = std::max<int64_t>(hs.n && !hs.separable ? hs.n : 0, ((int64_t)h->n_bool + h->n_real) / 4);
     const int threads = (int)std::max<int64_t>(256, std::min<int64_t>(1024, (per + 63) / 64 * 64));
-    hipLaunchKernelGGL(pgd_kernel, dim3(R), dim3(threads), lds, (hipStream_t)stream, View::of(a), View::of(b),
-                       View::of(grad_a), View::of(grad_b), as_cptr(h->d.real_lo), as_cptr(h->d.real_hi), eta_a, eta_b,
-                       gmap_sq, hs);
-    return launch_status("pgd kernel");
+    const int rows_max = rows_per_launch(R, threads);
+    for (int r0 = 0; r0 < R; r0 += rows_max) {
+        hipLaunchKernelGGL(pgd_kernel, dim3(std::min(R - r0, rows_max)), dim3(threads), lds, (hipStream_t)stream,
+                           rows_from(View::of(a), r0), rows_from(View::of(b), r0), rows_from(View::of(grad_a), r0),
+                           rows_from(View::of(grad_b), r0), as_cptr(h->d.real_lo), as_cptr(h->d.real_hi), eta_a, eta_b,
+                           gmap_sq ? gmap_sq + r0 : nullptr, hs);
+        if ((rc = launch_status("pgd kernel"))) return rc;
+        if (rows_max > R - r0) break;   // r0 + rows_max may pass INT32_MAX
+    }
+    return FSMT_OK;
 }
 
 fsmt_status round_and_check(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, int8_t *x, uint32_t *sat_bits,

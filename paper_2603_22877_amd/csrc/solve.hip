@@ -419,7 +419,7 @@ fsmt_status solve_impl(const fsmt_xbdd *const *insts, int32_t n_inst, const fsmt
             wg += (int64_t)d.R * k;
             if (k > 1) part_floats += (int64_t)d.R * 2 * k * ((int64_t)h->n_bool + h->n_real + 1);
         }
-        if (wg > INT32_MAX) return set_error(FSMT_ELIMIT, "too many restarts");
+        if (wg > INT32_MAX || wg * 64 * waves > (int64_t)UINT32_MAX) return set_error(FSMT_ELIMIT, "too many restarts");
         P.lds_nodes = G.maxn;
         P.lds_slots = G.maxs;
         P.state_floats = (int32_t)G.state_f;
@@ -469,7 +469,11 @@ fsmt_status solve_impl(const fsmt_xbdd *const *insts, int32_t n_inst, const fsmt
         int64_t wg_blocks = 0, row_floats = 0, work = 0;
         size_t wg_lds = 0;
         int wg_cf = 1;
-        for (int i : ib) work += (int64_t)states[i].a.rows * sweep_tasks(insts[i]);
+        int64_t restarts = 0;
+        for (int i : ib) {
+            work += (int64_t)states[i].a.rows * sweep_tasks(insts[i]);
+            restarts += states[i].a.rows;
+        }
         int lvl_nodes = 0, lvl_slots = 1, lvl_sym = 0;
         int maxn = 0, maxs = 1;
         size_t step_lds = 0;
@@ -512,7 +516,8 @@ fsmt_status solve_impl(const fsmt_xbdd *const *insts, int32_t n_inst, const fsmt
                 lvl_sym = std::max(lvl_sym, h->sym_max);
             }
             d.tile_base = tile_tasks;
-            d.slices = grid_slices(h, d.R, work, budget, n_cu);
+            // (a workgroup of 1,024 threads a restart at least: the launch stays below 2^32 threads)
+            d.slices = restarts <= (1 << 21) ? grid_slices(h, d.R, work, budget, n_cu) : 0;
             d.wg_base = wg_blocks;
             d.row_base = row_floats;
             d.tile_chunks = d.slices ? 0 : (h->n_tiles + 31) / 32;

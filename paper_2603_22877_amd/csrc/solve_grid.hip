@@ -199,22 +199,22 @@ __global__ void __launch_bounds__(1024) grid_wg_kernel(const GridInst *insts, in
 
 // Tiled constraints of the other instances: one wavefront per (restart, chunk of tiles).
 __global__ void __launch_bounds__(256) grid_tile_kernel(const GridInst *insts, int n_inst, GridShared S) {
-    const int lane = threadIdx.x & 63;
-    const int64_t task = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave_id();
-    if (task >= S.tile_tasks) return;
-    const int ii = find_base32(insts, n_inst, task, 4);
-    const GridInst &I = insts[ii];
-    const int64_t lt = task - I.tile_base;
-    const int r = (int)(lt / I.tile_chunks), id = (int)(lt - (int64_t)r * I.tile_chunks);
-    if (!S.stepping[I.rbase + r]) return;   // uniform
-    const TabView T = I.T;
-    const GlobalState st{View{I.a, I.R, T.n_bool, I.a_sr, 1}, View{I.b, I.R, T.n_real, I.b_sr, 1}};
-    const GlobalScatter sc{View{I.ga, I.R, T.n_bool, 1, I.R}, View{I.gb, I.R, T.n_real, 1, I.R}, 64};
-    const double kappa = S.kappas[I.level_done[r]];
-    const float oacc = wave_sum(tile_sweep<3, true>(T, st, sc, r, kappa, isinf(kappa), id, I.tile_chunks,
-                                                    [&](int c) -> float { return I.w[(int64_t)r * T.n_cons + c]; },
-                                                    [](int, float) {}, lane));
-    if (lane == 0 && oacc != 0.0f) atomic_add_f32(S.obj_acc + I.rbase + r, oacc);
+    const int lane = threadIdx.x & 63, wpb = blockDim.x >> 6;
+    for (int64_t task = (int64_t)blockIdx.x * wpb + wave_id(); task < S.tile_tasks; task += (int64_t)gridDim.x * wpb) {
+        const int ii = find_base32(insts, n_inst, task, 4);
+        const GridInst &I = insts[ii];
+        const int64_t lt = task - I.tile_base;
+        const int r = (int)(lt / I.tile_chunks), id = (int)(lt - (int64_t)r * I.tile_chunks);
+        if (!S.stepping[I.rbase + r]) continue;   // uniform
+        const TabView T = I.T;
+        const GlobalState st{View{I.a, I.R, T.n_bool, I.a_sr, 1}, View{I.b, I.R, T.n_real, I.b_sr, 1}};
+        const GlobalScatter sc{View{I.ga, I.R, T.n_bool, 1, I.R}, View{I.gb, I.R, T.n_real, 1, I.R}, 64};
+        const double kappa = S.kappas[I.level_done[r]];
+        const float oacc = wave_sum(tile_sweep<3, true>(T, st, sc, r, kappa, isinf(kappa), id, I.tile_chunks,
+                                                        [&](int c) -> float { return I.w[(int64_t)r * T.n_cons + c]; },
+                                                        [](int, float) {}, lane));
+        if (lane == 0 && oacc != 0.0f) atomic_add_f32(S.obj_acc + I.rbase + r, oacc);
+    }
 }
 
 // Big diagrams: one wavefront per (big constraint, chunk of restarts) over every instance,
@@ -453,7 +453,7 @@ static fsmt_status enqueue_level(const GridInst *d_insts, int n_inst, const Grid
             launch_sweep<4>(P, g, b, st, d_insts, n_inst, S);
         if ((rc = launch_status("grid sweep"))) return rc;
         if (S.tile_tasks > 0) {
-            hipLaunchKernelGGL(grid_tile_kernel, dim3((unsigned)((S.tile_tasks + 3) / 4)), dim3(256), 0, st, d_insts,
+            hipLaunchKernelGGL(grid_tile_kernel, dim3((unsigned)std::min<int64_t>((S.tile_tasks + 3) / 4, 1 << 20)), dim3(256), 0, st, d_insts,
                                n_inst, S);
             if ((rc = launch_status("grid tiles"))) return rc;
         }
