@@ -736,17 +736,33 @@ static WgGeom wg_geom(const fsmt_xbdd *h, int R, bool grad, int msg, size_t wave
         G.mixed = G.wide = true;
         G.waves = (int)std::min<int64_t>(16, tasks);
     }
-    // one slice (the call is one launch) unless the restarts leave most CUs idle and a wave
-    // would have many tasks; large instances write rows, which device atomics on every
-    // variable from every slice would cost more than
+    // Bucket tasks on many nearly empty buckets fill few of a wave's lanes with one restart; where
+    // the restarts fill the lanes instead and the message columns leave a workgroup few waves, the
+    // lane kernel is ahead (600 constraints of 587 shapes, 2,048 restarts: 7.8 ms a gradient
+    // against 9.2 ms here; 256 restarts 1.20 against 1.16).
+    if (G.waves <= 4 && wave_bytes && R >= 4 * n_cu && (int64_t)h->n_cons * 16 < h->n_pos) return WgGeom{};
+    // One slice (the call is one launch) unless the restarts leave CUs idle and one workgroup's
+    // rounds cost more than the zeroing launch and the atomics of several (about 3.5 us): a round
+    // of bucket tasks takes about 3 us (dependent gathers), of tiles 0.7 us (their loads are a tile
+    // ahead; clause pairs have a quarter of the others' atoms: 0.4). Several slices then leave a wave at most one task. One restart, us a gradient with a
+    // task a wave / four tasks a wave / one slice: 4,000 three-literal clauses of 153 shapes 13.6 /
+    // 35 / -, 6,000 two-selector ITEs 13.8 / 59 / -, scheduling 200 x 10 (67 tiles) 15 / - / 11.
+    // Large instances write rows, which device atomics on every variable from every slice would
+    // cost more than.
     const bool large = tasks >= (int64_t)8 * n_cu;
     G.slices = 1;
     if (R < n_cu) {
         int64_t s = n_cu / R;
-        if (!large) s = std::min<int64_t>(s, tasks / ((int64_t)G.waves * 4));
+        const double tile = h->tile_kinds == kTileClauses ? 0.4 : 0.7;
+        const double one = (3.0 * (double)(h->n_pos / 64) + tile * (double)h->n_tiles) / G.waves;
+        if (!large) s = one <= 3.5 ? 1 : std::min<int64_t>(s, 2 * tasks / G.waves);
         if (s >= 8) s = s / 8 * 8;
         G.slices = (int)std::max<int64_t>(1, s);
     }
+    // with more restarts than the CUs hold at 16 waves each, smaller workgroups: a wave runs several
+    // tasks after one load of the point (20 rectangles, 16,384 restarts: 130 us a gradient with 7
+    // waves, 58 with one; scheduling 200 x 10, 2,048 restarts: 65 with 16, 46 with four)
+    G.waves = (int)std::min<int64_t>(G.waves, std::max<int64_t>(1, (int64_t)32 * n_cu / R));
     G.mode = G.slices == 1 ? kStore : (grad && large) ? kRows : kAdd;
     G.lds = (state + (size_t)G.waves * wave_bytes + 15) / 16 * 16;
     return G;

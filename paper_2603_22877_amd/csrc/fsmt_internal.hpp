@@ -107,7 +107,8 @@ constexpr int kTileBitsMax = kPairMaxL;
 // kinds: 0 two dimensions with selectors, 1 one dimension with bits, 2 two dimensions with
 // bits, 3 one dimension with a Boolean per cell
 constexpr int kTileKinds = 4;
-constexpr uint32_t kTileBits = 6;   // mask of the kinds with bits
+constexpr uint32_t kTileBits = 6;      // mask of the kinds with bits
+constexpr uint32_t kTileClauses = 8;   // mask of kind 3
 // kind 3, words of a cell: Boolean id | row literal negated << 29 | column literal negated << 30
 // (-1: no cell); and per constraint (con_bool): Boolean id | negated << 29 | column's << 30
 constexpr int32_t kCellId = (1 << 29) - 1, kCellNeg = 1 << 29, kCellCol = 1 << 30;

@@ -171,7 +171,7 @@ static int grid_slices(const fsmt_xbdd *h, int R, int64_t work, size_t budget, i
 // 12.4, 15.0; 150 27.3, 19.4, 14.8, 15.3, 16.1; 300 93.9, 53.7, 32.0, 23.5, 21.1; scheduling
 // 200 x 10 9.4, 11.5, 12.2, 15.8, 21.1; 400 x 10 17.9, 17.5, 18.7, 23.6, 31.8.
 static double cluster_us(const fsmt_xbdd *h, int waves, int k) {
-    const double round = h->small_max_nodes > 0 ? 4.0 : (h->tile_kinds == 8u) ? 1.0 : 1.7;
+    const double round = h->small_max_nodes > 0 ? 4.0 : h->tile_kinds == kTileClauses ? 1.0 : 1.7;
     const double rounds = std::ceil((double)sweep_tasks(h) / ((double)waves * k));
     const double exchange = k > 1 ? 2.5 + 0.25 * k + 2e-4 * k * ((double)h->n_bool + h->n_real) : 0.0;
     return rounds * round + exchange;

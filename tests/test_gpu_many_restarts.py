@@ -1,10 +1,10 @@
-"""Restart counts whose one-workgroup-a-restart launches pass 2^32 threads: the calls are split and
-every restart gets the answer of a small call at its point."""
+"""Large restart counts (launches past 2^32 threads are split; workgroups shrink; nearly empty
+buckets go to the lane kernel): every restart gets the answer of a small call at its point."""
 import numpy as np
 import pytest
 
 import workloads as W
-from workloads.format import KIND_CARD_LE, KIND_CLAUSE, Builder, lit
+from workloads.format import KIND_CARD_LE, KIND_CLAUSE, KIND_XOR, Builder, lit
 
 from gpu_util import T, dev, torch
 
@@ -36,9 +36,22 @@ def _cards():
     return b.build()
 
 
+def _shapes():
+    """300 parities and cardinalities of nearly as many diagram shapes (node-by-node, LDS columns)."""
+    rng = np.random.default_rng(107)
+    b = Builder(40, 1, real_lo=np.full(1, -1.0), real_hi=np.full(1, 1.0))
+    for i in range(300):
+        n = int(rng.integers(4, 13))
+        lits = [lit(int(v), bool(rng.integers(0, 2))) for v in rng.choice(40, n, replace=False)]
+        b.add((KIND_XOR, KIND_CARD_LE)[i % 2], lits, n // 2 if i % 2 else 0)
+    return b.build()
+
+
+# past 2^32 threads; and where the workgroups get smaller, and shapes go to the lane kernel
 @pytest.mark.parametrize("make,R,accumulate", [(_clauses, (1 << 22) + 70, False), (_clauses, (1 << 22) + 70, True),
-                                               (_cards, 5_600_000, False)])
-def test_more_than_2_to_32_threads(make, R, accumulate):
+                                               (_cards, 5_600_000, False), (_clauses, 1100, False),
+                                               (_clauses, 8200, False), (_shapes, 1023, False), (_shapes, 1024, True)])
+def test_every_restart(make, R, accumulate):
     p = make()
     h = fsmt.xbdd_compile(p)
     few = 512
@@ -57,9 +70,9 @@ def test_more_than_2_to_32_threads(make, R, accumulate):
     for got, x in zip(out + [fobj], ref + [ref[0]]):
         x = x + (1.0 if accumulate and got is not fobj else 0.0)
         scale = float(x.abs().max())
-        for i in (0, reps // 2, reps - 2):   # whole blocks of the small call's restarts
+        for i in {0, R // few // 2, max(R // few - 1, 0)}:   # whole blocks of the small call's restarts
             assert float((got[i * few:(i + 1) * few] - x).abs().max()) <= 2e-6 * scale
-        last = R - (reps - 1) * few
-        assert float((got[(reps - 1) * few:] - x[:last]).abs().max()) <= 2e-6 * scale
+        last = R % few
+        assert last == 0 or float((got[R - last:] - x[:last]).abs().max()) <= 2e-6 * scale
     h.free()
 
