@@ -92,7 +92,6 @@ __global__ void __launch_bounds__(256) cop_kernel(CopArgs A) {
 
 // Tiled constraints of instances whose state does not fit LDS: one wave per (restart, chunk of
 // tiles), the state and the gradient in global memory.
-constexpr int kTileChunk = 32;
 constexpr int64_t kMaxBlocks = 1 << 20;   // of the kernels whose waves loop over their tasks
 template <bool kGrad>
 __global__ void __launch_bounds__(256) cop_tile_kernel(CopArgs A, int chunks) {
@@ -742,20 +741,17 @@ static WgGeom wg_geom(const fsmt_xbdd *h, int R, bool grad, int msg, size_t wave
     // against 9.2 ms here; 256 restarts 1.20 against 1.16).
     if (G.waves <= 4 && wave_bytes && R >= 4 * n_cu && (int64_t)h->n_cons * 16 < h->n_pos) return WgGeom{};
     // One slice (the call is one launch) unless the restarts leave CUs idle and one workgroup's
-    // rounds cost more than the zeroing launch and the atomics of several (about 3.5 us): a round
-    // of bucket tasks takes about 3 us (dependent gathers), of tiles 0.7 us (their loads are a tile
-    // ahead; clause pairs have a quarter of the others' atoms: 0.4). Several slices then leave a wave at most one task. One restart, us a gradient with a
-    // task a wave / four tasks a wave / one slice: 4,000 three-literal clauses of 153 shapes 13.6 /
-    // 35 / -, 6,000 two-selector ITEs 13.8 / 59 / -, scheduling 200 x 10 (67 tiles) 15 / - / 11.
+    // rounds (sweep_us) cost more than the zeroing launch and the atomics of several. Several slices
+    // then leave a wave at most one task. One restart, us a gradient with a task a wave / four tasks
+    // a wave / one slice: 4,000 three-literal clauses of 153 shapes 13.6 / 35 / -, 6,000
+    // two-selector ITEs 13.8 / 59 / -, scheduling 200 x 10 (65 tasks) 15 / - / 11.
     // Large instances write rows, which device atomics on every variable from every slice would
     // cost more than.
     const bool large = tasks >= (int64_t)8 * n_cu;
     G.slices = 1;
     if (R < n_cu) {
         int64_t s = n_cu / R;
-        const double tile = h->tile_kinds == kTileClauses ? 0.4 : 0.7;
-        const double one = (3.0 * (double)(h->n_pos / 64) + tile * (double)h->n_tiles) / G.waves;
-        if (!large) s = one <= 3.5 ? 1 : std::min<int64_t>(s, 2 * tasks / G.waves);
+        if (!large) s = sweep_us(h, G.waves) <= kSweepUsMin ? 1 : std::min<int64_t>(s, 2 * tasks / G.waves);
         if (s >= 8) s = s / 8 * 8;
         G.slices = (int)std::max<int64_t>(1, s);
     }
@@ -943,7 +939,7 @@ static fsmt_status cop_launch(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, doub
             if ((rc = launch_status("cop kernel"))) return rc;
         }
         if (h->n_tiles > 0) {
-            const int chunks = (h->n_tiles + kTileChunk - 1) / kTileChunk;
+            const int chunk = tile_chunk((int64_t)R * h->n_tiles, n_cu), chunks = (h->n_tiles + chunk - 1) / chunk;
             const dim3 tg((unsigned)std::min<int64_t>(((int64_t)R * chunks + 3) / 4, kMaxBlocks)), tb(256);
             if (grad) hipLaunchKernelGGL(cop_tile_kernel<true>, tg, tb, 0, st, A, chunks);
             else hipLaunchKernelGGL(cop_tile_kernel<false>, tg, tb, 0, st, A, chunks);

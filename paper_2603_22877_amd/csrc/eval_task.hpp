@@ -1081,12 +1081,12 @@ __device__ __forceinline__ float task_eval(const TabView &T, const TaskCtx &t, c
         if constexpr (kCF >= 3) {
             if (t.B.pad == -2)
                 return window_eval<kGrad>(T, t, T.gd[t.B.tpl].neg, st, kappa, hard, wc, sc, lane);
-        } else {
-            // no launch sends a window here (untiled_level); its template has neither a guarded
-            // disjunction's record nor room in the message store, so it must not fall through
-            if (t.B.pad == -2) return __builtin_nanf("");
         }
-        if (t.B.pad == -1) {
+        // (below level 3 no bucket holds a window: see closed_level. The two tests are the same
+        // there and after the window's; the solver's kernels spill 35 scalar registers more with
+        // the first, the per-call kernels 75 more with the second: 256 restarts of 4,000
+        // constraints of 2,800 shapes 1.66 against 2.01 ms a gradient)
+        if (kSlim ? t.B.pad == -1 : t.B.pad < 0) {
             const GdInfo g = load_gd(T.gd + t.B.tpl);
             const int NB = t.B.n_bslots, NA = t.B.n_slots - t.B.n_bslots;
             if (NB <= 1 && NA <= 2) return gd_eval_n<1, 2, kGrad, kSlim>(T, t, g, st, kappa, hard, wc, sc, lane);
@@ -1118,13 +1118,25 @@ inline int closed_level(const fsmt_xbdd *h) {
 }
 // The level of a launch that sweeps the untiled templates alone (their tiles run in a kernel of
 // their own): level 4 without a window leaves level 1's families.
-inline int untiled_level(int cf, bool windows) { return cf == 4 && !windows ? 1 : cf; }
+constexpr int untiled_level(int cf, bool windows) { return cf == 4 && !windows ? 1 : cf; }
 // The level that serves two instances of one launch.
-inline int closed_level_of(int a, int b) {
+constexpr int closed_level_of(int a, int b) {
     if (a == b) return a;
     if (a == 3 || b == 3 || a + b == 6) return 3;   // 2 and 4
     return a > b ? a : b;
 }
+// A kernel below level 3 takes a window's bucket for another family, so no launch with a window may
+// fall below it: closed_level gives 3 or 4 for an instance with windows, and neither function
+// loses that.
+constexpr bool keeps_windows() {
+    for (int a = 3; a <= 4; ++a) {
+        if (untiled_level(a, true) < 3) return false;
+        for (int b = 0; b <= 4; ++b)
+            if (closed_level_of(a, b) < 3 || closed_level_of(b, a) < 3) return false;
+    }
+    return true;
+}
+static_assert(keeps_windows(), "a launch with windows needs closed-form level 3 or 4");
 // The LDS store is used when asked for, and for instances with closed-form templates beside
 // node-by-node ones: their kernels carry both paths, and the generic templates in LDS leave
 // the closed forms the registers (scheduling 256 x 5: 4.2 ms per PGD step against 5.4 ms with
@@ -1132,8 +1144,22 @@ inline int closed_level_of(int a, int b) {
 inline bool lds_store(const fsmt_xbdd *h) {
     return h->lds_messages || ((h->n_pair > 0 || h->n_gd > 0 || h->n_window > 0) && h->small_max_nodes > 0);
 }
+// Tiles of one wave where the state is in global memory: as many as still give every CU 16 waves,
+// at most 32 (a run shares its column's values and gradient).
+inline int tile_chunk(int64_t tiles, int n_cu) {
+    const int64_t t = tiles / (16 * (int64_t)n_cu);
+    return (int)(t < 1 ? 1 : t > 32 ? 32 : t);
+}
 // 64-lane tasks of one restart's sweep.
 inline int64_t sweep_tasks(const fsmt_xbdd *h) { return (int64_t)h->n_pos / 64 + h->n_tiles; }
+// Modelled us of that sweep by one workgroup: a wave's bucket task takes about 3 us (dependent
+// gathers), a tile 0.7 us (its loads are a tile ahead; clause pairs have a quarter of the others'
+// atoms: 0.4). Below kSweepUsMin several workgroups cost more than they save.
+inline double sweep_us(const fsmt_xbdd *h, int waves) {
+    const double tile = h->tile_kinds == kTileClauses ? 0.4 : 0.7;
+    return (3.0 * (double)(h->n_pos / 64) + tile * (double)h->n_tiles) / waves;
+}
+constexpr double kSweepUsMin = 3.5;
 
 // Register variants need every atom in an inline record (the CSR path is compiled out).
 inline int msg_variant(int max_nodes, int max_slots, bool lds_only, bool all_inline) {

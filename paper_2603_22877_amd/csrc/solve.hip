@@ -151,16 +151,18 @@ static bool prefer_grid(const fsmt_xbdd *h, int R, int64_t R_batch, int waves_a,
 // Workgroups per restart of the grid schedule's workgroup sweep, or 0 where it does not apply
 // (node-by-node templates, an atom without an inline record (its kernel has the register store,
 // without the path through the atom table), a real state beyond the LDS): about two workgroups a
-// CU over the whole call, each with at least two tasks a wave. `work`: tasks x restarts of the
-// call.
+// CU over the whole call, each with at least two tasks a wave, or with a task for half of its
+// waves where one workgroup's rounds are long (4,000 three-literal clauses of 153 shapes, one
+// restart, 20 steps: 550 us with five slices). `work`: tasks x restarts of the call.
 static int grid_slices(const fsmt_xbdd *h, int R, int64_t work, size_t budget, int n_cu) {
     const int64_t tasks = sweep_tasks(h);
     const size_t lds = (size_t)h->n_real * 12;
     if (h->small_max_nodes > 0 || h->n_big > 0 || tasks == 0 || h->n_real == 0 || closed_level(h) < 1 ||
-        h->lds_messages || !h->all_inline || lds > std::min<size_t>(budget, 60000))
+        !h->all_inline || lds > std::min<size_t>(budget, 60000))
         return 0;
     const int64_t ideal = std::max<int64_t>(1, work / (2 * n_cu));   // tasks of one workgroup
-    const int64_t s = std::max<int64_t>(1, std::min((tasks + ideal - 1) / ideal, tasks / 32));
+    const int64_t most = sweep_us(h, 16) <= kSweepUsMin ? tasks / 32 : tasks / 8;
+    const int64_t s = std::max<int64_t>(1, std::min((tasks + ideal - 1) / ideal, most));
     return (int)std::min<int64_t>(s, INT32_MAX / std::max(1, R));
 }
 
@@ -520,7 +522,9 @@ fsmt_status solve_impl(const fsmt_xbdd *const *insts, int32_t n_inst, const fsmt
             d.slices = restarts <= (1 << 21) ? grid_slices(h, d.R, work, budget, n_cu) : 0;
             d.wg_base = wg_blocks;
             d.row_base = row_floats;
-            d.tile_chunks = d.slices ? 0 : (h->n_tiles + 31) / 32;
+            // 200 scheduling jobs, one restart, 20 steps: 345 us with chunks of 2 tiles, 1,070 with 32
+            const int tchunk = tile_chunk((int64_t)d.R * h->n_tiles, n_cu);
+            d.tile_chunks = d.slices ? 0 : (h->n_tiles + tchunk - 1) / tchunk;
             tile_tasks += (int64_t)d.R * d.tile_chunks;
             total_r += d.R;
             if (d.slices) {

@@ -58,9 +58,15 @@ __global__ void grid_begin_kernel(const GridInst *insts, int n_inst, GridShared 
     }
 }
 
+// Waves a SIMD that the sweep's registers have to leave room for (the compiler stops one register
+// short of some of them by itself: two-Boolean disjunctions at level 1, windows at level 3, a
+// quarter more time a sweep of 4,000 constraints of 2,800 shapes).
+template <int V, int kCF>
+constexpr int kSweepWaves = (V == kMsgMedium || V == kMsgLarge) ? 1 : kCF <= 1 ? 5 : kCF == 3 && V == kMsgSmall ? 2 : 3;
+
 // Forward + reverse sweep over every instance's (constraint, restart) lanes.
 template <int V, int kCF>
-__global__ void __launch_bounds__(256) grid_sweep_kernel(const GridInst *insts, int n_inst, GridShared S) {
+__global__ void __launch_bounds__(256, (kSweepWaves<V, kCF>)) grid_sweep_kernel(const GridInst *insts, int n_inst, GridShared S) {
     using Ms = typename MsgOf<V>::type;
     extern __shared__ float lds[];
     const int lane = threadIdx.x & 63, wib = wave_id(), wpb = blockDim.x >> 6;
@@ -124,11 +130,13 @@ __global__ void __launch_bounds__(256) grid_sweep_kernel(const GridInst *insts, 
 // (written out as the workgroup's row, added by the step kernel), the Booleans in global
 // memory. A Boolean that is a cell's own (tiles of kind 3) appears in no other constraint, so
 // the lane that has its gradient also takes its projected step here: no gradient array, no
-// atomics and no pass over the Booleans in the step kernel. Three scheduling instances of
-// 114,000 to 255,000 clauses at 16 restarts took 396 us a sweep and 219 us a step with
+// atomics and no pass over the Booleans in the step kernel. The other Booleans' gradient is added
+// to a row of the restart's own (restart-contiguous, the restarts' workgroups would add into the
+// same lines from every XCD: 20 rectangles, 16 restarts, 20 steps 418 us, 306 so). Three scheduling
+// instances of 114,000 to 255,000 clauses at 16 restarts took 396 us a sweep and 219 us a step with
 // restarts in the lanes (row-major states: one line per lane) and one block per restart.
 struct GridCellScatter {
-    View a, ga;        // ga: gradient of the free Booleans, restart-contiguous
+    View a, ga;        // ga: gradient of the free Booleans, a row per restart
     double *gb;
     float eta_a;
     float *gsq;        // this lane's gradient map of the Booleans it steps
@@ -176,7 +184,7 @@ __global__ void __launch_bounds__(1024) grid_wg_kernel(const GridInst *insts, in
     const View av{I.a, I.R, T.n_bool, I.a_sr, 1};
     float gsq = 0.0f, oacc = 0.0f;
     const MixedState st{av, sb};
-    const GridCellScatter sc{av, View{I.ga, I.R, T.n_bool, 1, I.R}, gb, S.eta_a, &gsq};
+    const GridCellScatter sc{av, View{I.ga, I.R, T.n_bool, T.n_bool, 1}, gb, S.eta_a, &gsq};
     const double kappa = S.kappas[I.level_done[r]];
     const bool hard = isinf(kappa);
     const gptr<float> wrow = I.w + (int64_t)r * T.n_cons;
@@ -197,7 +205,9 @@ __global__ void __launch_bounds__(1024) grid_wg_kernel(const GridInst *insts, in
     for (int j = threadIdx.x; j < m; j += blockDim.x) row[j] = (float)gb[j];
 }
 
-// Tiled constraints of the other instances: one wavefront per (restart, chunk of tiles).
+// Tiled constraints of the other instances: one wavefront per (restart, chunk of tiles); the
+// chunks are as long as still gives every CU 16 waves (runs share their column's values), at most
+// 32 tiles.
 __global__ void __launch_bounds__(256) grid_tile_kernel(const GridInst *insts, int n_inst, GridShared S) {
     const int lane = threadIdx.x & 63, wpb = blockDim.x >> 6;
     for (int64_t task = (int64_t)blockIdx.x * wpb + wave_id(); task < S.tile_tasks; task += (int64_t)gridDim.x * wpb) {
@@ -265,7 +275,9 @@ __global__ void __launch_bounds__(1024) grid_step_kernel(const GridInst *insts, 
     const bool wg = I.slices > 0;
     const int n = wg ? I.T.n_free : I.T.n_bool, m = I.T.n_real;
     const gptr<float> arow = I.a + (int64_t)r * I.a_sr, brow = I.b + (int64_t)r * I.b_sr;
-    const gptr<float> gacol = I.ga + r, gbcol = I.gb + r;   // element i at i * R
+    const gptr<float> gacol = wg ? I.ga + (int64_t)r * I.T.n_bool : I.ga + r;   // element i at i * ga_s
+    const gptr<float> gbcol = I.gb + r;                                         // element j at j * R
+    const int64_t ga_s = wg ? 1 : I.R;
     const float *rows = S.rows + I.row_base + (int64_t)r * I.slices * m;
     auto grad_b = [&](int j) -> float {
         if (!wg) {
@@ -286,10 +298,10 @@ __global__ void __launch_bounds__(1024) grid_step_kernel(const GridInst *insts, 
     float acc = 0.0f;
     for (int e = threadIdx.x; e < n; e += blockDim.x) {
         const int i = wg ? I.T.free_bool[e] : e;
-        const float x = arow[i], y = x - S.eta_a * gacol[(int64_t)i * I.R];
+        const float x = arow[i], y = x - S.eta_a * gacol[i * ga_s];
         const float p = y < -1.0f ? -1.0f : (y > 1.0f ? 1.0f : y);
         arow[i] = p;
-        gacol[(int64_t)i * I.R] = 0.0f;
+        gacol[i * ga_s] = 0.0f;
         const float q = (x - p) / S.eta_a;
         acc += q * q;
     }
@@ -357,7 +369,7 @@ __global__ void __launch_bounds__(256) grid_check_kernel(const GridInst *insts, 
         float h = S.rho * hr + (sat ? 0.0f : 1.0f);
         wv = wr;
         if (update) {
-            wv *= ErwaPow(S.gamma, S.rho)(h);
+            wv *= ErwaPow(S.gamma, S.rho, false)(h);   // one constraint a thread
             h = 1.0f;
             wr = wv;
         }
