@@ -147,8 +147,8 @@ __device__ __forceinline__ void wg_load_point(const View &a, const View &b, int 
 }
 
 // The workgroup's objective (lanes and waves summed in double) and gradient sums leave in one of
-// the three ways.
-template <bool kGrad, class G>
+// the three ways (kPart: rows are among them).
+template <bool kGrad, bool kPart = true, class G>
 __device__ __forceinline__ void wg_store(float oacc, int r, int n, int nm, const G *ga, float *obj, const View &va,
                                          const View &vb, int mode, float *part, double *opart) {
     __shared__ double part_o[16];
@@ -160,7 +160,7 @@ __device__ __forceinline__ void wg_store(float oacc, int r, int n, int nm, const
     if (threadIdx.x == 0) {
         double t = 0.0;
         for (int q = 0; q < wpb; ++q) t += part_o[q];
-        if (mode == kRows) opart[blockIdx.x] = t;
+        if (kPart && mode == kRows) opart[blockIdx.x] = t;
         else if (obj && mode == kStore) obj[r] = (float)t;
         else if (obj) atomic_add_f32(obj + r, (float)t);
     }
@@ -168,7 +168,7 @@ __device__ __forceinline__ void wg_store(float oacc, int r, int n, int nm, const
         float *row = part + (int64_t)blockIdx.x * nm;
         for (int e = threadIdx.x; e < nm; e += blockDim.x) {
             const float g = (float)ga[e];
-            if (mode == kRows) {
+            if (kPart && mode == kRows) {
                 row[e] = g;
             } else {
                 gref<float> dst = e < n ? va.at(r, e) : vb.at(r, e - n);
@@ -346,7 +346,7 @@ __global__ void __launch_bounds__(768) cop_big_wg_kernel(LevelArgs A, int slices
             oacc += wc * unsat;
         }
     }
-    wg_store<kGrad>(oacc, r, n, nm, ga, A.obj, A.ga, A.gb, mode, nullptr, nullptr);
+    wg_store<kGrad, false>(oacc, r, n, nm, ga, A.obj, A.ga, A.gb, mode, nullptr, nullptr);
 }
 
 // ------------------------------------------------------------------ small kernels
@@ -437,8 +437,9 @@ struct CheckArgs {
     int32_t *n_unsat;
 };
 
-// grid.x over 64-constraint groups (one wave each), grid.y over restarts.
-__global__ void __launch_bounds__(256) check_kernel(CheckArgs A) {
+// grid.x over 64-constraint groups (one wave each), grid.y over restarts. All latency: eight waves a
+// SIMD (two registers more would leave seven).
+__global__ void __launch_bounds__(256, 8) check_kernel(CheckArgs A) {
     const int lane = threadIdx.x & 63;
     const int64_t c64 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int r = blockIdx.y;

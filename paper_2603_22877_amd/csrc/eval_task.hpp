@@ -264,9 +264,21 @@ struct WaveScratch {
 
 __device__ __forceinline__ TileSet load_tset(cptr<TileSet> p) {
     static_assert(sizeof(TileSet) == 64, "tile set layout");
-    const i32x16 raw = *(cptr<i32x16>)p;
+    // field by field: copied as a whole at a per-lane address the record goes through memory (the
+    // check kernels' LDS, 16 KB a block; the solver's scratch)
+    const i32x4 a = ((cptr<i32x4>)p)[0], b = ((cptr<i32x4>)p)[1], c = ((cptr<i32x4>)p)[2];
     TileSet s;
-    __builtin_memcpy(&s, &raw, sizeof(s));
+    s.kind = a.x;
+    s.L = a.y;
+    s.tile0 = a.z;
+    s.n_tiles = a.w;
+    s.row_ent = b.x;
+    s.col_ent = b.y;
+    s.row_bits = b.z;
+    s.col_bits = b.w;
+    s.n_cells = c.x;
+    s.scale = __int_as_float(c.y);
+    s.cell0 = c.z;
     return s;
 }
 __device__ __forceinline__ TileEnt load_ent(cptr<TileEnt> p) {
@@ -1553,7 +1565,9 @@ __device__ __forceinline__ bool tile_check(const TabView &T, const St &st, int s
     for (int d = 0; d < 2; ++d) {
         if (d == 1 && S.kind == 1) break;
         const double lin = (double)st.bv(r, er.v[d]) - (double)st.bv(r, ec.v[d]);
-        const float rr = vr ? er.rhs[1][d] : er.rhs[0][d], rc = vc ? ec.rhs[1][d] : ec.rhs[0][d];
+        // values, not an lvalue to choose (which would keep both records in memory)
+        const float rr0 = er.rhs[0][d], rr1 = er.rhs[1][d], rc0 = ec.rhs[0][d], rc1 = ec.rhs[1][d];
+        const float rr = vr ? rr1 : rr0, rc = vc ? rc1 : rc0;
         sat = sat || lin - (double)rr <= 0.0 || -lin - (double)rc <= 0.0;
     }
     return sat;

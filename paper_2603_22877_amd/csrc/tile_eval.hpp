@@ -237,7 +237,7 @@ __device__ __forceinline__ float tile_run(const TabView &T, const TileSet &S, co
                 const float vlo = reduce8(v8, cj);
                 if (cj < L) sc.add(r, false, rbits[cj * 8], vlo);
                 const float vhi = reduce4(gx[0], gx[1], vb[8], vb[9], cj);
-                if (cj < D) sc.add(r, true, er.v[cj & 1], vhi);
+                if (cj < D) sc.add(r, true, (cj & 1) ? er.v[1] : er.v[0], vhi);
                 else if (cj >= 2 && cj < 4 && cj + 6 < L) sc.add(r, false, rbits[(cj + 6) * 8], vhi);
             }
         }
