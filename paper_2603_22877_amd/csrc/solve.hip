@@ -125,18 +125,51 @@ struct CallScratch {
 
 using namespace fsmt;
 
+// Modelled us of one iteration's sweep and exchange with k workgroups per restart, of total_r in the
+// launch: rounds of `waves` tasks (tiles 1.9 us a round, of clause pairs 1 us, bucket tasks 3.2 us,
+// 3 us and 0.45 us a node where node-by-node templates are among them), and for k > 1 the exchange of k partial
+// gradients through the coherence point, which all restarts share.
+// Measured (8 restarts, us per iteration at k = 1, 2, 4, 8, 16): placement 75 10.9, 11.5, 10.6,
+// 12.4, 15.0; 150 27.3, 19.4, 14.8, 15.3, 16.1; 300 93.9, 53.7, 32.0, 23.5, 21.1; scheduling
+// 200 x 10 9.4, 11.5, 12.2, 15.8, 21.1; 400 x 10 17.9, 17.5, 18.7, 23.6, 31.8. The same, 1 / 16
+// restarts: 4,000 clauses node by node 39.9, 25.0, 17.2, 15.0, 15.9 / 40.5, 25.6, 19.4, 19.0, 25.8;
+// 400 short parities 39.0, 26.4, 18.7, 15.7, 15.2 / 39.7, 26.8, 20.2, 19.3, 23.5; placement 150 node
+// by node, 16 restarts 260, 139, 76, 47, 41.
+static double cluster_us(const fsmt_xbdd *h, int waves, int64_t total_r, int k) {
+    const double bucket = h->small_max_nodes > 0 ? 3.0 + 0.45 * std::min(h->small_max_nodes, 20) : 3.2, tile = h->tile_kinds == kTileClauses ? 1.0 : 1.9;
+    const double tasks = (double)sweep_tasks(h);
+    const double round = tasks > 0.0 ? ((double)(h->n_pos / 64) * bucket + (double)h->n_tiles * tile) / tasks : 0.0;
+    const double exchange = 2.5 + 0.25 * k + 2e-4 * k * ((double)h->n_bool + h->n_real) + 0.006 * (double)total_r * k * std::sqrt((double)k);
+    return std::ceil(tasks / ((double)waves * k)) * round + (k > 1 ? exchange : 0.0);
+}
+
+// Workgroups per restart: the power of two with the smallest modelled iteration (of the slowest
+// instance) that keeps every workgroup resident.
+static int best_cluster(const fsmt_xbdd *const *insts, const std::vector<int> &ids, int waves, int64_t total_r,
+                        int64_t resident) {
+    int best_k = 1;
+    double best = 0.0;
+    for (int k = 1; k <= 16 && (k == 1 || total_r * k <= resident); k *= 2) {
+        double t = 0.0;
+        for (int i : ids) t = std::max(t, cluster_us(insts[i], waves, total_r, k));
+        if (k == 1 || t < best) {
+            best = t;
+            best_k = k;
+        }
+    }
+    return best_k;
+}
+
 // Schedule choice per instance (cost model in units of one wave task): the persistent
 // schedule needs the restart's state in LDS and costs ceil(tasks / waves) sequential tasks
 // per step on one CU; the grid schedule spreads tasks x restarts over all CUs (about 8 waves
 // each) and pays two launches per step (about 20 task-times).
 static bool prefer_grid(const fsmt_xbdd *h, int R, int64_t R_batch, int waves_a, int n_cu) {
-    // persistent: a restart's tasks over its cluster of k workgroups (k as chosen below, with
-    // every restart of the batch resident at once), plus the exchange of k partial
-    // gradients per step
+    // persistent: a restart's tasks over its cluster of k workgroups (the launch's own choice,
+    // with a workgroup a CU), plus the exchange of k partial gradients per step
     const double tasks_a = (double)sweep_tasks(h);                   // per restart, lane = constraint
     const int wa = std::max(1, waves_a);
-    int k = 1;
-    while (k < 16 && tasks_a >= 2.0 * (2 * k) * wa && R_batch * 2 * k <= n_cu) k *= 2;
+    const int k = best_cluster(&h, {0}, wa, R_batch, n_cu);
     const double exchange = k > 1 ? 4.0 + (double)(h->n_bool + h->n_real) * k / (wa * 64.0 * 16.0) : 0.0;
     const double t_a = std::ceil(tasks_a / (wa * k)) + exchange;
     // grid: every (constraint, restart) lane over the device, as many waves per CU as the
@@ -164,19 +197,6 @@ static int grid_slices(const fsmt_xbdd *h, int R, int64_t work, size_t budget, i
     const int64_t most = sweep_us(h, 16) <= kSweepUsMin ? tasks / 32 : tasks / 8;
     const int64_t s = std::max<int64_t>(1, std::min((tasks + ideal - 1) / ideal, most));
     return (int)std::min<int64_t>(s, INT32_MAX / std::max(1, R));
-}
-
-// Modelled us of one iteration's sweep and exchange with k workgroups per restart: rounds of
-// `waves` tasks (clause-pair tiles 1 us, other closed forms 1.7 us, node-by-node 4 us a
-// round), and for k > 1 the exchange of k partial gradients through the coherence point.
-// Measured (8 restarts, us per iteration at k = 1, 2, 4, 8, 16): placement 75 10.9, 11.5, 10.6,
-// 12.4, 15.0; 150 27.3, 19.4, 14.8, 15.3, 16.1; 300 93.9, 53.7, 32.0, 23.5, 21.1; scheduling
-// 200 x 10 9.4, 11.5, 12.2, 15.8, 21.1; 400 x 10 17.9, 17.5, 18.7, 23.6, 31.8.
-static double cluster_us(const fsmt_xbdd *h, int waves, int k) {
-    const double round = h->small_max_nodes > 0 ? 4.0 : h->tile_kinds == kTileClauses ? 1.0 : 1.7;
-    const double rounds = std::ceil((double)sweep_tasks(h) / ((double)waves * k));
-    const double exchange = k > 1 ? 2.5 + 0.25 * k + 2e-4 * k * ((double)h->n_bool + h->n_real) : 0.0;
-    return rounds * round + exchange;
 }
 
 // Geometry of one persistent launch over a set of instances.
@@ -375,18 +395,7 @@ fsmt_status solve_impl(const fsmt_xbdd *const *insts, int32_t n_inst, const fsmt
             if (k > 16 || (k > 1 && (total_r * k > resident_of(true) || !ib.empty())))
                 return set_error(FSMT_EUNSUPPORTED, "cluster of %d workgroups per restart cannot be co-resident", k);
         } else if (ib.empty()) {
-            // automatic: the power of two with the smallest modelled iteration that keeps every
-            // workgroup resident (see cluster_us)
-            const int64_t resd = resident_of(true);
-            double best = 0.0;
-            for (int q = 1; q <= 16 && (q == 1 || total_r * q <= resd); q *= 2) {
-                double t = 0.0;
-                for (int i : ia) t = std::max(t, cluster_us(insts[i], waves, q));
-                if (q == 1 || t < best) {
-                    best = t;
-                    k = q;
-                }
-            }
+            k = best_cluster(insts, ia, waves, total_r, resident_of(true));
             // the fixed scratch bounds the partial gradients
             auto part_bytes = [&]() {
                 int64_t f = 0;
