@@ -194,6 +194,12 @@ struct MixedScatter {
     }
 };
 
+// Data-parallel move of a float across lanes (rows outside kRows and lanes without a source get 0).
+template <int kCtrl, int kRows = 0xf>
+__device__ __forceinline__ float dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, kRows, 0xf, true));
+}
+
 // z = q.b - q0 of atom k for restart r (exact order, see atom_z_exact).
 template <class St>
 __device__ __forceinline__ double atom_z_state(const TabView &T, int k, const St &st, int r) {
@@ -1122,8 +1128,9 @@ __device__ __forceinline__ float task_eval(const TabView &T, const TaskCtx &t, c
 
 // Closed-form level of an instance: what its untiled templates need (see gd_level_of; 3 also
 // for untiled pair disjunctions, 0 when none has a closed form) and its tile kinds. Level 1 and
-// up carry tiles of kinds 0 and 3; levels 3 and 4 every kind and the window disjunctions, 4 beside the small guarded
-// disjunctions of level 1 only (the index encodings, whose pair constraints are all tiled).
+// up carry tiles of kinds 0 and 3; levels 3 and 4 every kind and the window disjunctions, 4 beside
+// the small guarded disjunctions of level 1 only (the index encodings, whose pair constraints are
+// all tiled).
 inline int closed_level(const fsmt_xbdd *h) {
     if ((h->tile_kinds & kTileBits) || h->n_window > 0) return h->gd_level <= 1 ? 4 : 3;
     return h->tile_kinds ? (h->gd_level > 1 ? h->gd_level : 1) : h->gd_level;
@@ -1282,19 +1289,15 @@ struct WaveObjAcc {
     }
 };
 
-template <int kCtrl, int kRows>
-__device__ __forceinline__ float dpp_rows(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, kRows, 0xf, true));
-}
 // Sum over the wave, in every lane (row shifts and row broadcasts, then lane 63's value: no
 // LDS round trips as a shuffle makes).
 __device__ __forceinline__ float wave_sum(float v) {
-    v += dpp_rows<0x111, 0xf>(v);   // row_shr:1
-    v += dpp_rows<0x112, 0xf>(v);
-    v += dpp_rows<0x114, 0xf>(v);
-    v += dpp_rows<0x118, 0xf>(v);
-    v += dpp_rows<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    v += dpp_rows<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+    v += dpp<0x111>(v);   // row_shr:1
+    v += dpp<0x112>(v);
+    v += dpp<0x114>(v);
+    v += dpp<0x118>(v);
+    v += dpp<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+    v += dpp<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
@@ -1437,10 +1440,6 @@ __device__ __forceinline__ float level_eval(const TabView &T, const LevelCtx &L,
 // way and dF/dP[literal s True] = sum_c A_s[c] (B[c+1] - B[c]) is a wave sum. No node table, no
 // LDS adds and no waits between literals: a level of the diagram pass took about 850 cycles
 // (dependent LDS round trips, few lanes busy) at 8 waves a CU.
-template <int kCtrl>
-__device__ __forceinline__ float wave_shift(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xf, 0xf, true));
-}
 template <class St, class Sc>
 __device__ __forceinline__ float sym_eval(const TabView &T, const LevelCtx &L, const St &st, const Sc &sc, int r,
                                           double kappa, bool hard, float wc, bool grad, float *rows, int lane) {
@@ -1473,7 +1472,7 @@ __device__ __forceinline__ float sym_eval(const TabView &T, const LevelCtx &L, c
     for (int s = 0; s < n; ++s) {
         const float t = lane_of(lt, s), f = lane_of(lf, s);
         if (grad && lane < w) rows[s * w + lane] = A;
-        A = f * A + t * wave_shift<0x138>(A);   // wave_shr:1
+        A = f * A + t * dpp<0x138>(A);   // wave_shr:1
     }
     const bool bad = lane <= n && ((falsem >> lane) & 1ull);
     const float F = wave_sum(bad ? A : 0.0f);
@@ -1493,7 +1492,7 @@ __device__ __forceinline__ float sym_eval(const TabView &T, const LevelCtx &L, c
 #pragma unroll
             for (int u = 0; u < K; ++u) {
                 const int s = s0 - u;
-                const float Bn = wave_shift<0x130>(B);   // wave_shl:1
+                const float Bn = dpp<0x130>(B);   // wave_shl:1
                 g[u] = a[u] * (Bn - B);
                 if (s >= 0) B = lane_of(lf, s) * B + lane_of(lt, s) * Bn;
             }

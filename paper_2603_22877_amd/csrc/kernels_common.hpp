@@ -250,8 +250,9 @@ __device__ __forceinline__ void sweep_rows_in_registers(float *y, float *pb, cpt
 // sweep; increments pb[m], ph[nnz] in LDS) until a sweep moves no coordinate by more than
 // 4e-7 (1 + |y|), or 256 sweeps. Projecting onto a class is projecting onto each member
 // independently (they share no variable), so the members of a class run on parallel lanes.
-// The sweeps run on the block's first wavefront alone, ordered by LDS waits instead of
-// block barriers. All threads of the block must call it.
+// Rows of two terms that fit kRowsPerThread registers a thread are swept by every wave
+// (sweep_rows_in_registers, a block barrier a class); other rows by the block's first wavefront
+// alone, ordered by LDS waits. All threads of the block must call it.
 __device__ __forceinline__ void project_dykstra(float *y, float *pb, float *ph, cptr<float> lo, cptr<float> hi,
                                                 int m, const HalfSpaces &hs) {
     if (hs.separable) {

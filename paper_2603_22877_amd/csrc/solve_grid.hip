@@ -208,7 +208,7 @@ __global__ void __launch_bounds__(1024) grid_wg_kernel(const GridInst *insts, in
 // Tiled constraints of the other instances: one wavefront per (restart, chunk of tiles); the
 // chunks are as long as still gives every CU 16 waves (runs share their column's values), at most
 // 32 tiles.
-__global__ void __launch_bounds__(256) grid_tile_kernel(const GridInst *insts, int n_inst, GridShared S) {
+__global__ void __launch_bounds__(256, 3) grid_tile_kernel(const GridInst *insts, int n_inst, GridShared S) {
     const int lane = threadIdx.x & 63, wpb = blockDim.x >> 6;
     for (int64_t task = (int64_t)blockIdx.x * wpb + wave_id(); task < S.tile_tasks; task += (int64_t)gridDim.x * wpb) {
         const int ii = find_base32(insts, n_inst, task, 4);

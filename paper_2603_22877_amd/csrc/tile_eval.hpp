@@ -5,8 +5,8 @@
 //
 // What bounds it: VALU issue, eight half_erfc (about 17 instructions and two transcendentals
 // each) of about 330 instructions a tile of kind 0: 1,200 rectangles at 16 restarts take 112 us
-// an iteration, level ends included (336 us with the buckets' guarded disjunctions). Against the guarded-disjunction task it
-// replaces: no atom records (264 bytes a constraint; here the constraint's id and weight), one
+// an iteration, level ends included (336 us with the buckets' guarded disjunctions). Against the
+// guarded-disjunction task it replaces: no atom records (264 bytes a constraint; here the constraint's id and weight), one
 // LDS scatter instruction instead of six, 64-bit linear forms once per dimension. 8 x 8 tiles
 // keep the triangle i < j of a pair set 99 % full at 1,200 entities (92 % at 150; 64 columns
 // a row would leave half of the lanes idle there) and a row's lanes within one DPP group.
@@ -15,19 +15,15 @@
 
 namespace fsmt {
 
-template <int kCtrl>
-__device__ __forceinline__ float dpp_of(float v) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), kCtrl, 0xf, 0xf, true));
-}
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppXor7 = 0x141, kDppDown4 = 0x104;
 
 // Sums of four values over each group of 8 lanes: lane j < 4 of the group gets value j's.
 __device__ __forceinline__ float reduce4(float v0, float v1, float v2, float v3, int j) {
     const bool b0 = j & 1, b1 = j & 2;
-    const float k0 = (b0 ? v1 : v0) + dpp_of<kDppXor1>(b0 ? v0 : v1);
-    const float k1 = (b0 ? v3 : v2) + dpp_of<kDppXor1>(b0 ? v2 : v3);
-    const float k = (b1 ? k1 : k0) + dpp_of<kDppXor2>(b1 ? k0 : k1);
-    return k + dpp_of<kDppDown4>(k);
+    const float k0 = (b0 ? v1 : v0) + dpp<kDppXor1>(b0 ? v0 : v1);
+    const float k1 = (b0 ? v3 : v2) + dpp<kDppXor1>(b0 ? v2 : v3);
+    const float k = (b1 ? k1 : k0) + dpp<kDppXor2>(b1 ? k0 : k1);
+    return k + dpp<kDppDown4>(k);
 }
 // Sums of eight values over each group of 8 lanes: lane j gets value j's (each step sends the
 // half of the values that the partner keeps; the partners j ^ 7, j ^ 2, j ^ 1 reach all 8).
@@ -35,10 +31,10 @@ __device__ __forceinline__ float reduce8(const float (&v)[8], int j) {
     const bool b0 = j & 1, b1 = j & 2, b2 = j & 4;
     float q[4], s[2];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) q[k] = (b2 ? v[k + 4] : v[k]) + dpp_of<kDppXor7>(b2 ? v[k] : v[k + 4]);
+    for (int k = 0; k < 4; ++k) q[k] = (b2 ? v[k + 4] : v[k]) + dpp<kDppXor7>(b2 ? v[k] : v[k + 4]);
 #pragma unroll
-    for (int k = 0; k < 2; ++k) s[k] = (b1 ? q[k + 2] : q[k]) + dpp_of<kDppXor2>(b1 ? q[k] : q[k + 2]);
-    return (b0 ? s[1] : s[0]) + dpp_of<kDppXor1>(b0 ? s[0] : s[1]);
+    for (int k = 0; k < 2; ++k) s[k] = (b1 ? q[k + 2] : q[k]) + dpp<kDppXor2>(b1 ? q[k] : q[k + 2]);
+    return (b0 ? s[1] : s[0]) + dpp<kDppXor1>(b0 ? s[0] : s[1]);
 }
 
 // Literal-false probability of the atom z <= 0 and e^{-u^2} (0 in hard mode), u = ks z.
@@ -320,9 +316,9 @@ __device__ __forceinline__ float cell_run(const TabView &T, const TileSet &S, co
         if constexpr (kGrad) {
             float gx = kd * ((hr ? wr0 * fr * mr : 0.0f) - (hc ? wc0 * fc * mc : 0.0f));
             gc -= gx;
-            gx += dpp_of<kDppXor1>(gx);
-            gx += dpp_of<kDppXor2>(gx);
-            gx += dpp_of<kDppXor7>(gx);
+            gx += dpp<kDppXor1>(gx);
+            gx += dpp<kDppXor2>(gx);
+            gx += dpp<kDppXor7>(gx);
             if (cj == 0) sc.add(r, true, er.v[0], gx);
             if (i0.word >= 0) {   // d P[literal False]/da = -+1/2
                 const float g = (hr ? (nr ? -0.5f : 0.5f) * (wr0 * lr) : 0.0f) + (hc ? (nc ? -0.5f : 0.5f) * (wc0 * lc) : 0.0f);
