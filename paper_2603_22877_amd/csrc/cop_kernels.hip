@@ -757,9 +757,11 @@ static WgGeom wg_geom(const fsmt_xbdd *h, int R, bool grad, int msg, size_t wave
         G.slices = (int)std::max<int64_t>(1, s);
     }
     // with more restarts than the CUs hold at 16 waves each, smaller workgroups: a wave runs several
-    // tasks after one load of the point (20 rectangles, 16,384 restarts: 130 us a gradient with 7
-    // waves, 58 with one; scheduling 200 x 10, 2,048 restarts: 65 with 16, 46 with four)
-    G.waves = (int)std::min<int64_t>(G.waves, std::max<int64_t>(1, (int64_t)32 * n_cu / R));
+    // tasks after one load of the point, about 10 us (20 rectangles, 16,384 restarts: 130 us a
+    // gradient with 7 waves, 58 with one; scheduling 200 x 10, 2,048 restarts: 65 with 16, 46 with
+    // four; 2,824 bucket tasks, 2,048 restarts: 13.2 ms with 16, 16.4 with four)
+    const int64_t few = (int64_t)std::ceil(sweep_us(h, 1) / 10.0);
+    G.waves = (int)std::min<int64_t>(G.waves, std::max<int64_t>({1, (int64_t)32 * n_cu / R, few}));
     G.mode = G.slices == 1 ? kStore : (grad && large) ? kRows : kAdd;
     G.lds = (state + (size_t)G.waves * wave_bytes + 15) / 16 * 16;
     return G;

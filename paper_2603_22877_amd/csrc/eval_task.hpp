@@ -1174,9 +1174,9 @@ inline int64_t sweep_tasks(const fsmt_xbdd *h) { return (int64_t)h->n_pos / 64 +
 // Modelled us of that sweep by one workgroup: a wave's bucket task takes about 3 us (dependent
 // gathers), a tile 0.7 us (its loads are a tile ahead; clause pairs have a quarter of the others'
 // atoms: 0.4). Below kSweepUsMin several workgroups cost more than they save.
-inline double sweep_us(const fsmt_xbdd *h, int waves) {
+inline double sweep_us(const fsmt_xbdd *h, int waves, bool tiles_only = false) {
     const double tile = h->tile_kinds == kTileClauses ? 0.4 : 0.7;
-    return (3.0 * (double)(h->n_pos / 64) + tile * (double)h->n_tiles) / waves;
+    return ((tiles_only ? 0.0 : 3.0 * (double)(h->n_pos / 64)) + tile * (double)h->n_tiles) / waves;
 }
 constexpr double kSweepUsMin = 3.5;
 

@@ -184,9 +184,11 @@ static bool prefer_grid(const fsmt_xbdd *h, int R, int64_t R_batch, int waves_a,
 // Workgroups per restart of the grid schedule's workgroup sweep, or 0 where it does not apply
 // (node-by-node templates, an atom without an inline record (its kernel has the register store,
 // without the path through the atom table), a real state beyond the LDS): about two workgroups a
-// CU over the whole call, each with at least two tasks a wave, or with a task for half of its
-// waves where one workgroup's rounds are long (4,000 three-literal clauses of 153 shapes, one
-// restart, 20 steps: 550 us with five slices). `work`: tasks x restarts of the call.
+// CU over the whole call, each with at least two tasks a wave; up to 24 with a task for half of
+// their waves where the bucket tasks' rounds are long (4,000 three-literal clauses of 153 shapes,
+// one restart, 20 steps: 550 us with five slices, 385 with 22). More cost the step kernel, which
+// adds their rows (600 rectangles, one restart: 1.06 ms with 90 slices, 2.26 with 340; 150
+// rectangles, 16 restarts: 0.49 with 6, 0.77 with 24). `work`: tasks x restarts of the call.
 static int grid_slices(const fsmt_xbdd *h, int R, int64_t work, size_t budget, int n_cu) {
     const int64_t tasks = sweep_tasks(h);
     const size_t lds = (size_t)h->n_real * 12;
@@ -194,7 +196,8 @@ static int grid_slices(const fsmt_xbdd *h, int R, int64_t work, size_t budget, i
         !h->all_inline || lds > std::min<size_t>(budget, 60000))
         return 0;
     const int64_t ideal = std::max<int64_t>(1, work / (2 * n_cu));   // tasks of one workgroup
-    const int64_t most = sweep_us(h, 16) <= kSweepUsMin ? tasks / 32 : tasks / 8;
+    const bool buckets = sweep_us(h, 16) - sweep_us(h, 16, true) > kSweepUsMin;
+    const int64_t most = buckets ? std::max(tasks / 32, std::min<int64_t>(24, tasks / 8)) : tasks / 32;
     const int64_t s = std::max<int64_t>(1, std::min((tasks + ideal - 1) / ideal, most));
     return (int)std::min<int64_t>(s, INT32_MAX / std::max(1, R));
 }
