@@ -921,10 +921,13 @@ static fsmt_status cop_launch(const fsmt_xbdd *h, fsmt_view a, fsmt_view b, doub
         const int rows_max = wg.slices > 1 ? R : rows_per_launch(R, 64 * wg.waves);
         for (int r0 = 0, nr; r0 < R; r0 += nr) {
             nr = std::min(R - r0, rows_max);
-            CopArgs B = A;
-            for (View *v : {&B.a, &B.b, &B.w, &B.unsat, &B.ga, &B.gb}) *v = rows_from(*v, r0);
-            if (B.obj) B.obj += r0;
-            void *args[] = {(void *)&B, (void *)&wg.slices, (void *)&wg.mode, (void *)&accumulate, (void *)&part, (void *)&opart};
+            CopArgs *P = &A, B;
+            if (nr < R) {
+                P = &(B = A);
+                for (View *v : {&B.a, &B.b, &B.w, &B.unsat, &B.ga, &B.gb}) *v = rows_from(*v, r0);
+                if (B.obj) B.obj += r0;
+            }
+            void *args[] = {(void *)P, (void *)&wg.slices, (void *)&wg.mode, (void *)&accumulate, (void *)&part, (void *)&opart};
             const hipError_t le = hipLaunchKernel(cop_wg_fn(grad, msg, cf, wg.wide, wg.mixed), dim3((unsigned)(nr * wg.slices)),
                                                   dim3(64 * wg.waves), args, wg.lds, st);
             if (le != hipSuccess) return set_error(FSMT_EHIP, "cop kernel (state in LDS): %s", hipGetErrorString(le));
