@@ -270,8 +270,14 @@ struct WaveScratch {
 
 __device__ __forceinline__ TileSet load_tset(cptr<TileSet> p) {
     static_assert(sizeof(TileSet) == 64, "tile set layout");
-    // field by field: copied as a whole at a per-lane address the record goes through memory (the
-    // check kernels' LDS, 16 KB a block; the solver's scratch)
+    const i32x16 raw = *(cptr<i32x16>)p;
+    TileSet s;
+    __builtin_memcpy(&s, &raw, sizeof(s));
+    return s;
+}
+// The record at a per-lane address, field by field: copied as a whole it goes through memory (the
+// check kernels' LDS, 16 KB a block; the solver's scratch).
+__device__ __forceinline__ TileSet load_tset_lane(cptr<TileSet> p) {
     const i32x4 a = ((cptr<i32x4>)p)[0], b = ((cptr<i32x4>)p)[1], c = ((cptr<i32x4>)p)[2];
     TileSet s;
     s.kind = a.x;
@@ -1529,7 +1535,7 @@ __device__ __forceinline__ float sym_eval(const TabView &T, const LevelCtx &L, c
 // whose two products by +-1 are exact.
 template <class St>
 __device__ __forceinline__ bool tile_check(const TabView &T, const St &st, int set, int row, int c, int r) {
-    const TileSet S = load_tset(T.tset + set);   // per lane
+    const TileSet S = load_tset_lane(T.tset + set);
     const int col = T.con_col[c];
     const TileEnt er = load_ent(T.tent + row), ec = load_ent(T.tent + col);
     if (S.kind == 3) {   // its literal, or its side's atom
